@@ -121,7 +121,16 @@ typedef enum { UM_BCOL_FIRST_FIT = 0, UM_BCOL_RECOLOUR = 1, UM_BCOL_MIN = 2 } um
  * hanging (um_plan_errors, um_plan_set_wait_limit).  Each block's flag counts the executions it has
  * completed (all flags advance together), so the launch needs no host-side
  * counter and may be captured in a HIP graph and replayed.  Supported for STAGE_ALL with one or two
- * elements per lane; a plan must not execute concurrently with itself. */
+ * elements per lane; a plan must not execute concurrently with itself.
+ * Edge-loop plans with the LDS-DMA gather or SoA data need no order between
+ * blocks where no cell has more than 8 edges and no block stages more than
+ * 1023 cells or nodes: they run the owner kernel, in which each cell is
+ * incremented by one of its blocks only (the first that touches it), which
+ * evaluates all edges around it, those on its border too.  Such a launch has
+ * no waits, no flags and no colour rounds; its results are reproducible bit
+ * for bit in every um_tcmode.  The block and thread colours, the launch
+ * order by colour and the statistics below describe the plan's blocks all
+ * the same. */
 typedef enum { UM_SCHED_COLOUR_LAUNCHES = 0, UM_SCHED_DATAFLOW = 1 } um_schedule;
 /* How a DATAFLOW block of the edge loop moves its staged data from HBM to
  * LDS (Section 2.2's gather step).  REGISTERS: each lane loads a staged
@@ -397,7 +406,19 @@ typedef enum {
     UM_EXP_RUNS_B = 14,
     UM_EXP_PRED_OFFSETS = 15,   /* DATAFLOW: int32[n_blocks+1], launch position order:
                                    the blocks each position waits for              */
-    UM_EXP_PREDS = 16           /* DATAFLOW: int32[...]: their launch positions      */
+    UM_EXP_PREDS = 16,          /* DATAFLOW: int32[...]: their launch positions      */
+    UM_EXP_OWNER_RECORDS = 17,  /* plans of the owner kernel (um_schedule): per block in
+                                   launch order, int32[n][10]: first row of sides, owned
+                                   cells, staged cells, staged nodes, first id and
+                                   length of the run of cells, then of nodes, first
+                                   node item, items                                  */
+    UM_EXP_OWNER_IDS = 18,      /* int32[n][stride]: the items, ids of the staged cells
+                                   past the run, padded, then of the nodes           */
+    UM_EXP_OWNER_SIDES = 19     /* int32[rows][4 or 8][4]: per owned cell and side (in the
+                                   order of their addition), the
+                                   staged positions of the neighbour and of the two
+                                   nodes, and the cell's slot in the edge; -1 for a
+                                   missing side                                      */
 } um_export_field;
 
 /* ---------------------------------------------------------------- context */

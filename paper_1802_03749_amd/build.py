@@ -24,7 +24,7 @@ LIB = os.path.join(PKG, "libumesh.so")
 ROCM = os.environ.get("ROCM_PATH", "/opt/rocm")
 ARCH = "gfx950"
 
-HOST_SOURCES = ["reorder.cpp", "planner.cpp", "planner_step.cpp"]
+HOST_SOURCES = ["reorder.cpp", "planner.cpp", "planner_step.cpp", "planner_owner.cpp"]
 HIP_SOURCES = ["api.cpp", "kernels_lf2d.hip", "kernels_hex.hip", "kernels_step.hip",
                "kernels_util.hip"]
 
@@ -33,7 +33,7 @@ HIP_SOURCES = ["api.cpp", "kernels_lf2d.hip", "kernels_hex.hip", "kernels_step.h
 HIP_FLAGS = ["-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}",
              "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
              "-munsafe-fp-atomics", "-Wall", "-Wno-unused-result"]
-HOST_FLAGS = ["-O2", "-std=c++17", "-fPIC", "-Wall"]
+HOST_FLAGS = ["-O2", "-std=c++17", "-fPIC", "-Wall", "-pthread"]
 
 
 def _run(cmd, verbose):

@@ -105,9 +105,9 @@ T *upload(const std::vector<T> &v, int64_t &bytes) {
 }
 
 void free_device_plan(Plan &p) {
-    void *bufs[13] = {p.dp.emap,  p.dp.binfo, p.dp.stg_c,    p.dp.stg_n, p.dp.loc,
+    void *bufs[16] = {p.dp.emap,  p.dp.binfo, p.dp.stg_c,    p.dp.stg_n, p.dp.loc,
                       p.dp.crun,  p.dp.nrun,  p.dp.pred_off, p.dp.preds, p.dp.frec,
-                      p.dp.flags, p.dp.err,   p.dp.partials};
+                      p.dp.flags, p.dp.err,   p.dp.partials, p.dp.own_rec, p.dp.own_ids, p.dp.own_words};
     for (void *b : bufs)
         if (b) hipFree(b);
     p.dp = DevicePlan{};
@@ -363,6 +363,12 @@ LaunchArgs launch_args(Plan &p, const double *params, int32_t nparams, void *str
     la.frec = p.dp.frec;
     la.gather = p.hp.gather;
     la.sum_first = p.hp.n_sum_first > 0;
+    la.own_rec = p.dp.own_rec;
+    la.own_ids = p.dp.own_ids;
+    la.own_words = p.dp.own_words;
+    la.own_stride = p.hp.owner.id_stride;
+    la.own_threads = p.hp.owner.threads;
+    la.own_quads = p.hp.owner.ring ? 0 : p.hp.owner.quads;
     la.flags = p.dp.flags;
     la.err = p.dp.err;
     la.wait_ticks = p.wait_ticks;
@@ -646,6 +652,9 @@ um_status um_plan_build(um_ctx ctx, int32_t kernel, const um_arg *args, int32_t 
                          "LDS-DMA gather: HIER plans with the DATAFLOW schedule on AoS data only");
                 build_host_plan(c, p->ea, iter_set, o, p->hp);
                 p->hp.gather = o.gather;
+                if (p->hp.strategy == UM_STRAT_HIER && p->hp.schedule == UM_SCHED_DATAFLOW &&
+                    (o.gather == UM_GATHER_LDS_DMA || p->ea.layout == UM_SOA))
+                    build_owner_plan(c, p->ea, o, p->hp);
             } else if (is_step_kernel(kernel)) {
                 if (o.gather != UM_GATHER_REGISTERS)
                     fail(UM_ERR_UNSUPPORTED, "LDS-DMA gather: edge flux loop only");
@@ -660,14 +669,20 @@ um_status um_plan_build(um_ctx ctx, int32_t kernel, const um_arg *args, int32_t 
             if (c.device >= 0) {
                 DeviceGuard g(c.device);
                 int64_t bytes = 0;
+                const bool own = p->hp.owner.use;  // its kernel needs nothing else
+                p->dp.own_rec = upload(p->hp.owner.rec, bytes);
+                p->dp.own_ids = upload(p->hp.owner.ids, bytes);
+                p->dp.own_words = upload(p->hp.owner.words, bytes);
                 p->dp.emap = upload(p->hp.emap, bytes);
-                p->dp.binfo = upload(p->hp.binfo, bytes);
-                p->dp.stg_c = upload(p->hp.stg_c, bytes);
-                p->dp.stg_n = upload(p->hp.stg_n, bytes);
-                p->dp.crun = upload(p->hp.crun, bytes);
-                p->dp.nrun = upload(p->hp.nrun, bytes);
-                p->dp.loc = upload(p->hp.loc, bytes);
-                if (p->hp.schedule == UM_SCHED_DATAFLOW && !p->hp.binfo.empty()) {
+                if (!own) {
+                    p->dp.binfo = upload(p->hp.binfo, bytes);
+                    p->dp.stg_c = upload(p->hp.stg_c, bytes);
+                    p->dp.stg_n = upload(p->hp.stg_n, bytes);
+                    p->dp.crun = upload(p->hp.crun, bytes);
+                    p->dp.nrun = upload(p->hp.nrun, bytes);
+                    p->dp.loc = upload(p->hp.loc, bytes);
+                }
+                if (!own && p->hp.schedule == UM_SCHED_DATAFLOW && !p->hp.binfo.empty()) {
                     p->dp.pred_off = upload(p->hp.pred_off, bytes);
                     p->dp.preds = upload(p->hp.preds, bytes);
                     p->dp.frec = upload(p->hp.frec, bytes);
@@ -838,6 +853,47 @@ um_status um_plan_export(um_plan plan, int32_t field, int32_t *host_out, int64_t
                 tmp[4 * s + 3] = int32_t((h >> 1) & 0x7FFu);
             }
             break;
+        case UM_EXP_OWNER_RECORDS:
+            if (!hp.owner.use) fail(UM_ERR_STATE, "not a plan of the owner kernel");
+            for (const OwnRec &r : hp.owner.rec) {
+                const int32_t *w = &r.word_off;
+                tmp.insert(tmp.end(), w, w + 10);
+            }
+            break;
+        case UM_EXP_OWNER_IDS:
+            if (!hp.owner.use) fail(UM_ERR_STATE, "not a plan of the owner kernel");
+            v = &hp.owner.ids;
+            break;
+        case UM_EXP_OWNER_SIDES:
+            if (!hp.owner.use) fail(UM_ERR_STATE, "not a plan of the owner kernel");
+            for (const OwnRec &r : hp.owner.rec)
+                for (int32_t i = 0; i < r.n_own; ++i) {
+                    auto side = [&](uint32_t h, uint32_t a, uint32_t b, uint32_t slot, bool there) {
+                        const uint32_t v[4] = {h, a, b, slot};
+                        for (uint32_t x : v) tmp.push_back(there ? int32_t(x) : -1);
+                    };
+                    if (hp.owner.ring) {
+                        const uint32_t *w = &hp.owner.words[3 * size_t(r.word_off) + i];
+                        const uint32_t w0 = w[0], w1 = w[r.n_own], w2 = w[2 * r.n_own];
+                        const uint32_t h[4] = {w0 & 0x3FFu, (w0 >> 10) & 0x3FFu,
+                                               (w0 >> 20) & 0x3FFu, w1 & 0x3FFu};
+                        const uint32_t c[4] = {(w1 >> 10) & 0x3FFu, (w1 >> 20) & 0x3FFu,
+                                               w2 & 0x3FFu, (w2 >> 10) & 0x3FFu};
+                        const uint32_t slot[4] = {(w0 >> 30) & 1u, w0 >> 31, (w1 >> 30) & 1u,
+                                                  w1 >> 31};
+                        for (int k = 0; k < 4; ++k)
+                            side(h[k], c[k], c[(k + 1) & 3], slot[k], h[k] != NO_CELL);
+                    } else {
+                        const int32_t n = 4 * hp.owner.quads;
+                        for (int32_t k = 0; k < n; ++k) {
+                            const uint32_t s =
+                                hp.owner.words[(size_t(r.word_off) + i) * n + k];
+                            side(s & 0x3FFu, (s >> 10) & 0x3FFu, (s >> 20) & 0x3FFu,
+                                 (s >> 30) & 1u, s != NO_SIDE);
+                        }
+                    }
+                }
+            break;
         default: fail(UM_ERR_ARG, "unknown export field %d", field);
         }
         (void)c;
@@ -889,14 +945,16 @@ void exec_plan(Plan &p, const double *params, int32_t nparams, void *stream, boo
                     fail(UM_ERR_ARG, "static scratch: %lld dataflow blocks need %lld bytes, "
                          "limit %lld", (long long)(words - 1), (long long)(256 + 4 * words),
                          (long long)STATIC_SCRATCH_BYTES);
-                static_ctl = reinterpret_cast<int32_t *>(base);
-                la.err = static_ctl;
-                la.flags = reinterpret_cast<int32_t *>(base + 256);
-                const hipError_t e1 = zero_words(static_ctl, 4, la.stream);
-                const hipError_t e2 = zero_words(la.flags, words, la.stream);
-                if (e1 != hipSuccess || e2 != hipSuccess)
-                    fail(UM_ERR_HIP, "clearing the static scratch: %s",
-                         hipGetErrorString(e1 != hipSuccess ? e1 : e2));
+                if (!hp.owner.use) {  // the owner kernel has no flags
+                    static_ctl = reinterpret_cast<int32_t *>(base);
+                    la.err = static_ctl;
+                    la.flags = reinterpret_cast<int32_t *>(base + 256);
+                    const hipError_t e1 = zero_words(static_ctl, 4, la.stream);
+                    const hipError_t e2 = zero_words(la.flags, words, la.stream);
+                    if (e1 != hipSuccess || e2 != hipSuccess)
+                        fail(UM_ERR_HIP, "clearing the static scratch: %s",
+                             hipGetErrorString(e1 != hipSuccess ? e1 : e2));
+                }
             } else if (la.n_partials > 0) {
                 if (8 * int64_t(la.n_partials) > STATIC_SCRATCH_BYTES)
                     fail(UM_ERR_ARG, "static scratch: %d partial sums need %lld bytes, limit %lld",
@@ -971,7 +1029,10 @@ void exec_plan(Plan &p, const double *params, int32_t nparams, void *stream, boo
             }
         } else if (hp.strategy == UM_STRAT_HIER && hp.schedule == UM_SCHED_DATAFLOW) {
             // the execution number is kept and advanced on the device
-            one(LAUNCH_HIER_FLOW, 0, int32_t(hp.blk_order.size()), hp.lds_max);
+            if (hp.owner.use)
+                one(LAUNCH_OWNER, 0, int32_t(hp.owner.rec.size()), hp.owner.lds);
+            else
+                one(LAUNCH_HIER_FLOW, 0, int32_t(hp.blk_order.size()), hp.lds_max);
         } else if (hp.strategy == UM_STRAT_HIER) {
             for (int32_t c = 0; c + 1 < int32_t(hp.bcol_off.size()); ++c)
                 if (hp.bcol_off[c + 1] > hp.bcol_off[c])

@@ -59,6 +59,59 @@ __device__ __forceinline__ void lf2d_flux_nocontract(Real xa0, Real xa1, Real xb
     UM_LF2D_FLUX_BODY
 }
 
+// Velocity, pressure and energy plus pressure of a state.  The roundings here
+// and in lf2d_flux_out are written out: they are those that lf2d_flux gets
+// from the compiler's contractions.
+template <typename Real>
+struct Flow {
+    Real u, v, p, h;
+};
+
+template <typename Real>
+__device__ __forceinline__ Flow<Real> flow_of(const Real q[4], Real gm1) {
+#pragma clang fp contract(off)
+    const Real ri = Real(1) / q[0];
+    Flow<Real> s;
+    s.u = q[1] * ri;
+    s.v = q[2] * ri;
+    const Real e = fma(Real(-0.5), fma(q[1], s.u, q[2] * s.v), q[3]);
+    s.p = e * gm1;
+    s.h = fma(e, gm1, q[3]);
+    return s;
+}
+
+// lf2d_flux as it leaves the cell with state q and flow s into the one with
+// state r and flow t; the normal of (a, b) points that way, and `second` says
+// that the cell left is the edge's second one.  Seen from the other side
+// (states swapped, a and b swapped, second inverted) it is exactly the
+// negative: every value rounded only changes its sign.
+template <typename Real>
+__device__ __forceinline__ void lf2d_flux_out(Real xa0, Real xa1, Real xb0, Real xb1,
+                                              const Real q[4], const Flow<Real> &s,
+                                              const Real r[4], const Flow<Real> &t, Real aq,
+                                              Real ar, Real eps, bool second, Real f[4]) {
+#pragma clang fp contract(off)
+    const Real half = Real(0.5);
+    const Real nx = xb1 - xa1;
+    const Real ny = xa0 - xb0;
+    const Real U = fma(s.v, ny, s.u * nx);
+    const Real V = fma(t.v, ny, t.u * nx);
+    const Real hm = half * (eps * half * (aq + ar));
+    Real F[4];
+    if constexpr (sizeof(Real) == 8) {
+        F[0] = q[0] * U + r[0] * V;
+        F[3] = s.h * U + t.h * V;
+    } else {
+        // binary32: bit for bit lf2d_flux, which rounds cell 1's product only
+        F[0] = second ? fma(r[0], V, q[0] * U) : fma(q[0], U, r[0] * V);
+        F[3] = second ? fma(t.h, V, s.h * U) : fma(s.h, U, t.h * V);
+    }
+    F[1] = fma(s.p, nx, q[1] * U) + fma(t.p, nx, r[1] * V);
+    F[2] = fma(s.p, ny, q[2] * U) + fma(t.p, ny, r[2] * V);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) f[k] = fma(q[k] - r[k], hm, half * F[k]);
+}
+
 // Element g of a dim-4 / dim-2 dat in AoS ([n][dim]) or SoA ([dim][n])
 // layout; AoS uses 16-byte vector loads.
 template <int LAYOUT, typename Real>

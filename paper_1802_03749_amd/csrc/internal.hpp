@@ -149,6 +149,44 @@ struct FlowRec {
 };
 static_assert(sizeof(FlowRec) == 256, "FlowRec is 256 bytes");
 
+// The owner kernel of the edge loop (planner_owner.cpp): per block, in
+// launch order, the cells it owns and the cells and nodes it stages.  Staged
+// cells are the owned ones, then the others; the first c_run of them are
+// consecutive ids from c_start, the rest are listed, and the nodes likewise.
+// The listed ids (cells padded to a whole wavefront, then from node_item on
+// the nodes) sit at a fixed stride per block, so that they are loaded
+// together with the record.
+struct OwnRec {
+    int32_t word_off;          // owned cells of the earlier blocks
+    int32_t n_own, nc, nn;     // owned cells, staged cells, staged nodes
+    int32_t c_start, c_run, n_start, n_run;
+    int32_t node_item, n_items;
+    int32_t pad[2];
+};
+static_assert(sizeof(OwnRec) == 48, "OwnRec is 12 words");
+
+// An owned cell's sides, out of staged positions of 10 bits.  Ring form, for
+// cells of at most four sides that lie around it: neighbours h0..h3 (NO_CELL
+// for a missing side) and corners c0..c3, side k running from corner k to
+// corner (k + 1) mod 4 with its normal out of the cell, and slot k = 1 if the
+// cell is that edge's second one:
+//   h0 | h1 << 10 | h2 << 20 | slot0 << 30 | slot1 << 31,
+//   h3 | c0 << 10 | c1 << 20 | slot2 << 30 | slot3 << 31,  c2 | c3 << 10
+// in three planes per block.  General form: 4 * quads words per cell, each
+// h | a << 10 | b << 20 | slot << 30, NO_SIDE for a missing side.
+constexpr uint32_t NO_SIDE = 0xFFFFFFFFu, NO_CELL = 0x3FFu;
+constexpr int32_t MAX_OWNER_POINTS = 1023;     // staged cells, and staged nodes
+constexpr int32_t MAX_SIDE_QUADS = 2;          // at most 8 sides per cell
+
+struct OwnerPlan {
+    bool use = false, ring = false;
+    int32_t threads = 0, quads = 1, id_stride = 0, n_own_max = 0;
+    int64_t lds = 0;
+    std::vector<OwnRec> rec;
+    std::vector<int32_t> ids;                  // [n_blocks][id_stride]
+    std::vector<uint32_t> words;               // side words, blocks in launch order
+};
+
 struct HostPlan {
     int32_t strategy = 0, staging = 0, tcmode = 0, block_size = 0;
     int32_t ept = 1, threads = 0;              // HIER: elements per lane, lanes per block
@@ -181,10 +219,13 @@ struct HostPlan {
     int32_t max_tcol = 0;
     double avg_tcol = 0.0, reuse = 0.0;
     int64_t lds_max = 0, staged_total = 0;
+    OwnerPlan owner;                           // DATAFLOW edge loop without waits
 };
 
 void build_host_plan(const Ctx &ctx, const EdgeArgs &ea, int32_t iter_set,
                      const um_plan_opts &o, HostPlan &hp);
+// Fills hp.owner of a dataflow edge plan where its blocks allow it.
+void build_owner_plan(const Ctx &ctx, const EdgeArgs &ea, const um_plan_opts &o, HostPlan &hp);
 void build_host_plan_hex(const Ctx &ctx, const HexArgs &ha, int32_t iter_set,
                          const um_plan_opts &o, HostPlan &hp);
 
@@ -203,6 +244,7 @@ void build_host_plan_step(const Ctx &ctx, int32_t kernel, const StepArgs &sa, in
 
 // LDS bytes a block needs for the given counts.
 int64_t lf2d_lds_bytes(int32_t staging, int32_t dtype, int64_t n_cells, int64_t n_nodes);
+int64_t owner_lds_bytes(int32_t dtype, int64_t n_cells, int64_t n_nodes);
 int64_t hex_lds_bytes(int64_t n_nodes, bool dataflow);
 
 // ----------------------------------------------------------------- device
@@ -217,6 +259,9 @@ struct DevicePlan {
     int32_t *flags = nullptr;                       // DATAFLOW: completion epochs per block
     int32_t *err = nullptr;                         // DATAFLOW: [timeouts, epoch of the
                                                     //  last timeout, unused x2]
+    OwnRec *own_rec = nullptr;                      // owner kernel
+    int32_t *own_ids = nullptr;
+    uint32_t *own_words = nullptr;
     double *partials = nullptr;                     // UPDATE: one sum per workgroup
     int64_t bytes = 0;
 };

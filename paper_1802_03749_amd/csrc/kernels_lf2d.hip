@@ -932,6 +932,223 @@ __attribute__((amdgpu_waves_per_eu(sizeof(Real) == 4 ? 8 : 1))) void hier_dma_ke
     if (tid == 0) __hip_atomic_store(flags + pos, epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// store4 for values that nothing reads again in this launch: the nontemporal
+// hint keeps their lines from displacing staged data that neighbouring
+// blocks still want.
+template <int LAYOUT>
+__device__ __forceinline__ void store4_once(double *__restrict__ a, int64_t n, int64_t g,
+                                            const double v[4]) {
+    if constexpr (LAYOUT == UM_AOS) {
+        f64x2 *p = reinterpret_cast<f64x2 *>(a + 4 * g);
+        __builtin_nontemporal_store(f64x2{v[0], v[1]}, p);
+        __builtin_nontemporal_store(f64x2{v[2], v[3]}, p + 1);
+    } else {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) __builtin_nontemporal_store(v[k], a + k * n + g);
+    }
+}
+
+// Owner kernel: the dataflow schedule's blocks without an order between them
+// (planner_owner.cpp).  A block stages the cells and nodes around the cells it
+// owns, and lane i adds the outgoing fluxes of owned cell i to its residual in
+// registers, in a fixed order, and stores it.  Every edge is evaluated from
+// both of its cells; the two values are bitwise each other's negative
+// (lf2d_flux_out), so what leaves one cell enters the other.
+// The waiting kernels are bound by their chain of block colours (a block's
+// residuals pass through up to five blocks, each a gather, the colour rounds
+// and a flag apart) wherever the sweep is not long enough to hide it; here a
+// block is one gather, one barrier and one store, bound by memory.  A 16x16-
+// cell block stages 320 cells instead of 289 but writes 256 residuals instead
+// of 289, and evaluating each flux twice stays below the memory's time.  One
+// sweep, three meshes in turn (waiting kernels -> here): binary64 200x100
+// cells 14.8 -> 4.9 us (what submitting a launch takes), 1200x600 31.6 -> 19.4,
+// 2400x1200 80.9 -> 72.4 (5.8 TB/s of counted traffic), binary32 1133x711 29.5
+// -> 15.9, SoA (staged through registers) 907x613 28.7 -> 15.1.  Blocks that
+// are chunks of the RCM order stage 1.5 times the cells: 33.5 -> 28.6.
+template <int LAYOUT, bool RING, typename Real>
+__global__ __launch_bounds__(1024) void owner_kernel(const OwnRec *__restrict__ recs,
+                                                     const int32_t *__restrict__ ids,
+                                                     int32_t id_stride,
+                                                     const uint32_t *__restrict__ words,
+                                                     int32_t quads, Dats<Real> d, double gm1d,
+                                                     double epsd) {
+    constexpr bool F64 = sizeof(Real) == 8;
+    constexpr bool DMA = LAYOUT == UM_AOS;
+    extern __shared__ double lds[];
+    const Real gm1 = Real(gm1d), eps = Real(epsd);
+    const int32_t pos = int32_t(blockIdx.x);
+    const int tid = int(threadIdx.x), T = int(blockDim.x), lane = tid & 63;
+    const int32_t *__restrict__ my_ids = ids + int64_t(pos) * id_stride;
+    // this lane's listed id, together with the record
+    int32_t id0 = tid < id_stride ? my_ids[tid] : 0;
+    const OwnRec &rec = recs[pos];
+    const int n_own = rec.n_own, nc = rec.nc, nn = rec.nn;
+    const int c_run = rec.c_run, n_run = rec.n_run, node_item = rec.node_item;
+    const int n_items = rec.n_items;
+    const int32_t c_start = rec.c_start, n_start = rec.n_start;
+
+    Real *q_a = reinterpret_cast<Real *>(lds);  // F64: [nc] x (q0, q1); F32: [nc] x q[4]
+    Real *q_b = q_a + 2 * nc;                   // F64: [nc] x (q2, q3)
+    Real *x_a = q_a + 4 * nc;                   // F64: [nn] x (x, y); F32: [nn] x
+    Real *x_b = x_a + nn;                       // F32: [nn] y
+    uint32_t *adt_w = reinterpret_cast<uint32_t *>(x_a + 2 * nn);  // F64: [2][nc] words
+    const __amdgpu_buffer_rsrc_t rq = rsrc_of(d.q, 4 * sizeof(Real) * d.C);
+    const __amdgpu_buffer_rsrc_t ra = rsrc_of(d.adt, sizeof(Real) * d.C);
+    const __amdgpu_buffer_rsrc_t rx = rsrc_of(d.x, 2 * sizeof(Real) * d.N);
+
+    // side words and residual of this lane's owned cell
+    const uint32_t *__restrict__ my_words =
+        words + int64_t(rec.word_off) * (RING ? 3 : 4 * quads);
+    auto sides_of = [&](int j) {
+        if constexpr (RING)
+            return make_uint4(my_words[tid], my_words[n_own + tid], my_words[2 * n_own + tid], 0u);
+        else
+            return reinterpret_cast<const uint4 *>(my_words)[tid * quads + j];
+    };
+    uint4 w;
+    double r[4];
+    int32_t own_id = 0;
+    if (tid < n_own) {
+        own_id = tid < c_run ? c_start + tid : my_ids[tid - c_run];
+        w = sides_of(0);
+        load4<LAYOUT>(d.res, d.C, own_id, r);
+    }
+    auto cell_in = [&](int t0, int32_t g) {
+        if constexpr (DMA && F64) {
+            dma<16>(rq, q_a + 2 * t0, 32 * g);
+            dma<16>(rq, q_b + 2 * t0, 32 * g + 16);
+            dma<4>(ra, adt_w + t0, 8 * g);
+            dma<4>(ra, adt_w + nc + t0, 8 * g + 4);
+        } else if constexpr (DMA) {
+            dma<16>(rq, q_a + 4 * t0, 16 * g);
+            dma<4>(ra, adt_w + t0, 4 * g);
+        } else {
+            const int t = t0 + lane;
+            Real v[4];
+            load4<LAYOUT>(d.q, d.C, g, v);
+            const Real a = d.adt[g];
+            if constexpr (F64) {
+                *reinterpret_cast<f64x2 *>(q_a + 2 * t) = f64x2{v[0], v[1]};
+                *reinterpret_cast<f64x2 *>(q_b + 2 * t) = f64x2{v[2], v[3]};
+                const uint64_t b = __builtin_bit_cast(uint64_t, a);
+                adt_w[t] = uint32_t(b);
+                adt_w[nc + t] = uint32_t(b >> 32);
+            } else {
+                *reinterpret_cast<float4 *>(q_a + 4 * t) = make_float4(v[0], v[1], v[2], v[3]);
+                adt_w[t] = __builtin_bit_cast(uint32_t, a);
+            }
+        }
+    };
+    auto node_in = [&](int t0, int32_t g) {
+        if constexpr (DMA && F64) {
+            dma<16>(rx, x_a + 2 * t0, 16 * g);
+        } else if constexpr (DMA) {
+            dma<4>(rx, x_a + t0, 8 * g);
+            dma<4>(rx, x_b + t0, 8 * g + 4);
+        } else {
+            const int t = t0 + lane;
+            Real a, b;
+            load2<LAYOUT>(d.x, d.N, g, a, b);
+            if constexpr (F64) {
+                *reinterpret_cast<f64x2 *>(x_a + 2 * t) = f64x2{a, b};
+            } else {
+                x_a[t] = a;
+                x_b[t] = b;
+            }
+        }
+    };
+    const int tw = __builtin_amdgcn_readfirstlane(tid - lane);
+    const int npass = c_run > n_run ? c_run : n_run;
+    for (int t0 = tw; t0 < npass; t0 += T) {
+        const int t = t0 + lane;
+        if (t < c_run) cell_in(t0, c_start + t);
+        if (t < n_run) node_in(t0, n_start + t);
+    }
+    for (int j0 = tw; j0 < n_items; j0 += T) {
+        const int32_t g = j0 == tw ? id0 : (j0 + lane < n_items ? my_ids[j0 + lane] : 0);
+        if (j0 < node_item) {
+            if (c_run + j0 + lane < nc) cell_in(c_run + j0, g);
+        } else {
+            const int t0 = n_run + j0 - node_item;
+            if (t0 + lane < nn) node_in(t0, g);
+        }
+    }
+    __builtin_amdgcn_s_waitcnt(0);
+    __syncthreads();
+
+    auto state = [&](int t, Real q[4], Real &a) {
+        if constexpr (F64) {
+            const f64x2 lo = *reinterpret_cast<const f64x2 *>(q_a + 2 * t);
+            const f64x2 hi = *reinterpret_cast<const f64x2 *>(q_b + 2 * t);
+            q[0] = lo.x; q[1] = lo.y; q[2] = hi.x; q[3] = hi.y;
+            a = __builtin_bit_cast(double, uint64_t(adt_w[t]) | (uint64_t(adt_w[nc + t]) << 32));
+        } else {
+            const float4 v = *reinterpret_cast<const float4 *>(q_a + 4 * t);
+            q[0] = v.x; q[1] = v.y; q[2] = v.z; q[3] = v.w;
+            a = __builtin_bit_cast(float, adt_w[t]);
+        }
+    };
+    auto node = [&](int t, Real &x0, Real &x1) {
+        if constexpr (F64) {
+            const f64x2 v = *reinterpret_cast<const f64x2 *>(x_a + 2 * t);
+            x0 = v.x; x1 = v.y;
+        } else {
+            x0 = x_a[t]; x1 = x_b[t];
+        }
+    };
+    if (tid < n_own) {
+        Real q[4], a;
+        state(tid, q, a);
+        const dev::Flow<Real> own = dev::flow_of(q, gm1);
+        // adds what leaves through the side (xa, xb) towards staged cell h
+        auto side = [&](int h, Real xa0, Real xa1, Real xb0, Real xb1, bool second) {
+            Real qh[4], ah, f[4];
+            state(h, qh, ah);
+            dev::lf2d_flux_out(xa0, xa1, xb0, xb1, q, own, qh, dev::flow_of(qh, gm1), a, ah, eps,
+                               second, f);
+#pragma unroll
+            for (int c = 0; c < 4; ++c) r[c] += double(f[c]);
+        };
+        // one side at a time: unrolled, the loads of all sides are issued first
+        // and their registers leave room for fewer wavefronts
+        if constexpr (RING) {
+            Real xa0, xa1, xb0, xb1, xc0, xc1;
+            node(int((w.y >> 10) & 0x3FFu), xa0, xa1);
+            xc0 = xa0; xc1 = xa1;
+            uint32_t hs = w.x, next = (w.y >> 20) & 0x3FFu, rest = w.z;
+            uint32_t slots = (w.x >> 30) | ((w.y >> 30) << 2);
+#pragma unroll 1
+            for (int k = 0; k < 4; ++k) {
+                if (k < 3) {
+                    node(int(next), xb0, xb1);
+                } else {
+                    xb0 = xc0; xb1 = xc1;
+                }
+                const uint32_t h = hs & 0x3FFu;
+                if (h != NO_CELL) side(int(h), xa0, xa1, xb0, xb1, slots & 1u);
+                xa0 = xb0; xa1 = xb1;
+                next = rest & 0x3FFu;
+                rest >>= 10;
+                hs = k == 2 ? w.y : hs >> 10;
+                slots >>= 1;
+            }
+        } else {
+#pragma unroll 1
+            for (int k = 0; k < 4 * quads; ++k) {
+                if (k == 4) w = sides_of(1);
+                const uint32_t s = w.x;
+                w.x = w.y; w.y = w.z; w.z = w.w;
+                if (s == NO_SIDE) continue;
+                Real xa0, xa1, xb0, xb1;
+                node(int((s >> 10) & 0x3FFu), xa0, xa1);
+                node(int((s >> 20) & 0x3FFu), xb0, xb1);
+                side(int(s & 0x3FFu), xa0, xa1, xb0, xb1, (s >> 30) & 1u);
+            }
+        }
+        store4_once<LAYOUT>(d.res, d.C, own_id, r);
+    }
+}
+
 template <int LAYOUT, typename Real>
 __global__ __launch_bounds__(1024) void gcol_kernel(const int4 *__restrict__ emap, int32_t begin,
                                                    int32_t end, Dats<Real> d, double gm1,
@@ -1080,11 +1297,26 @@ hipError_t launch_flow(const LaunchArgs &la, int32_t nblocks, int64_t lds, const
     return hipErrorInvalidValue;
 }
 
+template <int LAYOUT, bool RING, typename Real>
+hipError_t launch_owner(const LaunchArgs &la, int32_t nblocks, int64_t lds, const Dats<Real> &d) {
+    clear_stale_error();
+    const hipError_t ea =
+        allow_lds(reinterpret_cast<const void *>(owner_kernel<LAYOUT, RING, Real>), lds);
+    if (ea != hipSuccess) return ea;
+    hipLaunchKernelGGL((owner_kernel<LAYOUT, RING, Real>), dim3(nblocks), dim3(la.own_threads),
+                       size_t(lds), la.stream, la.own_rec, la.own_ids, la.own_stride,
+                       la.own_words, la.own_quads, d, la.gm1, la.eps);
+    return hipGetLastError();
+}
+
 template <int LAYOUT, typename Real>
 hipError_t launch_typed(const LaunchArgs &la, int which, int32_t begin, int32_t end, int64_t lds) {
     const Dats<Real> d{static_cast<const Real *>(la.x), static_cast<const Real *>(la.q),
                        static_cast<const Real *>(la.adt), la.res, la.N, la.C};
     if (which == LAUNCH_HIER) return launch_hier<LAYOUT>(la, end - begin, begin, lds, d);
+    if (which == LAUNCH_OWNER)
+        return la.own_quads == 0 ? launch_owner<LAYOUT, true>(la, end - begin, lds, d)
+                                 : launch_owner<LAYOUT, false>(la, end - begin, lds, d);
     if (which == LAUNCH_HIER_FLOW) {
         if (la.staging != UM_STAGE_ALL || (la.ept != 1 && la.ept != 2) || end - begin <= 0)
             return hipErrorInvalidValue;

@@ -12,7 +12,7 @@
 namespace um {
 
 enum { LAUNCH_HIER = 0, LAUNCH_GCOL = 1, LAUNCH_ATOMIC = 2, LAUNCH_DEBUG = 3,
-       LAUNCH_HIER_FLOW = 4, LAUNCH_DIRECT = 5, LAUNCH_REDUCE = 6 };
+       LAUNCH_HIER_FLOW = 4, LAUNCH_DIRECT = 5, LAUNCH_REDUCE = 6, LAUNCH_OWNER = 7 };
 
 struct LaunchArgs {
     hipStream_t stream;
@@ -34,6 +34,10 @@ struct LaunchArgs {
     int32_t gather;           // HIER, DATAFLOW: um_gather
     int32_t sum_first;        // DATAFLOW edge loop: 1 if any block sums before its wait
     int32_t *flags, *err;  // DATAFLOW: completion flags; err = control words [4]
+    const OwnRec *own_rec;    // owner kernel: per launch position
+    const int32_t *own_ids;
+    const uint32_t *own_words;
+    int32_t own_stride, own_threads, own_quads;  // quads 0: sides in ring form
     uint64_t wait_ticks;   // DATAFLOW: longest wait for one neighbour (100 MHz ticks)
     double qinf[4];        // BOUNDARY_FLUX: far-field state
     double *partials;      // UPDATE: per-workgroup sums

@@ -25,6 +25,11 @@ int64_t lf2d_lds_bytes(int32_t staging, int32_t dtype, int64_t nc, int64_t nn) {
     return inc + nc * 5 * w + nn * 2 * w;  // q[4], adt per cell; x[2] per node
 }
 
+int64_t owner_lds_bytes(int32_t dtype, int64_t nc, int64_t nn) {
+    const int64_t w = dtype == UM_F64 ? 8 : 4;
+    return nc * 5 * w + nn * 2 * w;  // q[4], adt per cell; x[2] per node
+}
+
 // Stable counting sort of 0..n-1 by small integer keys; returns the order
 // and fills offsets[key] (size nkeys + 1).
 std::vector<int32_t> counting_order(const std::vector<int32_t> &key, int32_t nkeys,

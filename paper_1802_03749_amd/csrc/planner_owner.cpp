@@ -1,0 +1,358 @@
+// Host plans of the owner kernels: the dataflow schedule's blocks without an
+// order between them.  Every point that a loop increments belongs to one of
+// the blocks that touch it, and that block evaluates every element around
+// the point; elements on a border between blocks are evaluated by each
+// block that owns one of their points.  No point is then written by two
+// blocks, so a sweep is one launch of blocks that neither wait nor colour.
+#include <algorithm>
+#include <cstdint>
+#include <cstdlib>
+#include <exception>
+#include <memory>
+#include <new>
+#include <thread>
+
+#include "internal.hpp"
+
+namespace um {
+
+namespace {
+
+// Launch order of nb blocks in G = 8 or the caller's number of XCD groups:
+// the k-th workgroup takes the next block of id range k mod G (G equal
+// ranges), or, once that range is used up, of the range with most left.
+std::vector<int32_t> interleaved_blocks(int32_t nb, int32_t G) {
+    std::vector<int32_t> order(nb), next(G), end(G);
+    for (int32_t g = 0; g < G; ++g) {
+        // ids b with floor(b * G / nb) == g
+        next[g] = int32_t((int64_t(g) * nb + G - 1) / G);
+        end[g] = int32_t((int64_t(g + 1) * nb + G - 1) / G);
+    }
+    for (int32_t k = 0; k < nb; ++k) {
+        int32_t g = k % G;
+        if (next[g] == end[g])
+            for (int32_t h = 0; h < G; ++h)
+                if (end[h] - next[h] > end[g] - next[g]) g = h;
+        order[k] = next[g]++;
+    }
+    return order;
+}
+
+// The same over windows of 8 * 32 consecutive blocks: each XCD takes 32
+// neighbouring blocks and all of them stay in one part of the mesh.
+std::vector<int32_t> windowed_blocks(int32_t nb) {
+    constexpr int32_t X = 8, B = 32;
+    std::vector<int32_t> order(nb);
+    for (int32_t k = 0; k < nb; ++k) {
+        const int32_t w = k / (X * B) * (X * B), i = k - w;
+        order[k] = w + X * B <= nb ? w + i % X * B + i / X : k;
+    }
+    return order;
+}
+
+// Length of the run of consecutive ids that starts the sorted list's first n.
+int32_t leading_run(const std::vector<int32_t> &v, size_t n) {
+    size_t r = n > 0;
+    while (r < n && v[r] == v[r - 1] + 1) ++r;
+    return int32_t(r);
+}
+
+// Moves the sorted list's longest run to its front; returns its length.
+int32_t longest_run_first(std::vector<int32_t> &v) {
+    size_t best = 0, len = 0;
+    for (size_t i = 0; i < v.size();) {
+        size_t j = i + 1;
+        while (j < v.size() && v[j] == v[j - 1] + 1) ++j;
+        if (j - i > len) {
+            best = i;
+            len = j - i;
+        }
+        i = j;
+    }
+    std::rotate(v.begin(), v.begin() + best, v.begin() + best + len);
+    return int32_t(len);
+}
+
+uint16_t *zeroed(int64_t n) {
+    void *p = std::calloc(size_t(std::max<int64_t>(n, 1)), sizeof(uint16_t));
+    if (!p) throw std::bad_alloc();
+    return static_cast<uint16_t *>(p);
+}
+
+// One side of an owned cell: staged positions of the neighbour and of the
+// nodes a, b (the normal of (a, b) points out of the cell), slot of the cell.
+struct Side {
+    uint32_t h, a, b, slot;
+};
+
+// Arranges the n sides around the cell (side k from corner k to corner k + 1
+// mod 4) as s[0..3], missing ones with h = NO_CELL; false if they don't fit.
+bool arrange(const Side *side, int32_t n, Side s[4], uint32_t corner[4]) {
+    if (n > 4) return false;
+    // usually each side's end is the start of one that follows in the list or
+    // closes the ring: follow them from the first
+    for (int32_t c = 0; c < 4; ++c) s[c] = Side{NO_CELL, 0, 0, 0};
+    corner[0] = corner[1] = corner[2] = corner[3] = 0;
+    if (n == 4) {
+        int32_t at = 0, left = 0xE, k = 0;  // sides 1..3 are still to be placed
+        for (; k < 4; ++k) {
+            s[k] = side[at];
+            corner[k] = side[at].a;
+            if (k == 3) break;
+            const uint32_t end = side[at].b;
+            int32_t j = 1;
+            while (j < 4 && !((left >> j & 1) && side[j].a == end)) ++j;
+            if (j == 4) break;
+            left &= ~(1 << j);
+            at = j;
+        }
+        if (k == 3 && s[3].b == corner[0]) return true;
+    }
+    bool used[4] = {false, false, false, false};
+    int32_t first = 0;
+    // start where no side ends, if there is such a place
+    for (int32_t i = 0; i < n; ++i) {
+        bool ends = false;
+        for (int32_t j = 0; j < n; ++j) ends |= j != i && side[j].b == side[i].a;
+        if (!ends) {
+            first = i;
+            break;
+        }
+    }
+    int32_t k = 0, at = n > 0 ? first : -1, placed = 0;
+    for (int32_t c = 0; c < 4; ++c) {
+        s[c] = Side{NO_CELL, 0, 0, 0};
+        corner[c] = 0;
+    }
+    bool set[4] = {false, false, false, false};
+    auto put = [&](int32_t c, uint32_t v) {
+        c &= 3;
+        if (set[c] && corner[c] != v) return false;
+        set[c] = true;
+        corner[c] = v;
+        return true;
+    };
+    while (placed < n) {
+        if (at < 0) {  // the next side starts anew, one corner further
+            ++k;
+            for (int32_t j = 0; j < n && at < 0; ++j)
+                if (!used[j]) at = j;
+        }
+        if (k > 3 || !put(k, side[at].a) || !put(k + 1, side[at].b)) return false;
+        s[k++] = side[at];
+        used[at] = true;
+        ++placed;
+        int32_t next = -1;
+        for (int32_t j = 0; j < n && next < 0; ++j)
+            if (!used[j] && side[j].a == side[at].b) next = j;
+        at = next;
+    }
+    return true;
+}
+
+// Runs work(b0, b1) over [0, nb) in as many ranges as threads are worth it
+// for E elements, each on its own thread; the largest result.
+template <typename F>
+auto in_ranges(int32_t nb, int64_t E, F work) {
+    using R = decltype(work(0, 0));
+    const int64_t most = std::min<int64_t>(8, std::thread::hardware_concurrency());
+    const int32_t n = int32_t(std::max<int64_t>(1, std::min<int64_t>({most, nb, E / 10000})));
+    std::vector<R> got(n, R{});
+    std::vector<std::exception_ptr> failed(n);
+    auto part = [&](int32_t i) {
+        try {
+            got[i] = work(int32_t(int64_t(i) * nb / n), int32_t(int64_t(i + 1) * nb / n));
+        } catch (...) {
+            failed[i] = std::current_exception();
+        }
+    };
+    std::vector<std::thread> threads;
+    for (int32_t i = 1; i < n; ++i) {
+        try {
+            threads.emplace_back(part, i);
+        } catch (const std::exception &) {  // no more threads to be had
+            part(i);
+        }
+    }
+    part(0);
+    for (std::thread &t : threads) t.join();
+    for (const std::exception_ptr &e : failed)
+        if (e) std::rethrow_exception(e);
+    return *std::max_element(got.begin(), got.end());
+}
+
+}  // namespace
+
+void build_owner_plan(const Ctx &ctx, const EdgeArgs &ea, const um_plan_opts &o, HostPlan &hp) {
+    const Map &mc = ctx.maps[ea.map_c];
+    const Map &mn = ctx.maps[ea.map_n];
+    const int64_t C = ctx.sets[mc.to].size, N = ctx.sets[mn.to].size;
+    const int64_t E = hp.n_elem;
+    const int32_t nb = int32_t(hp.blk_off.size()) - 1;
+    OwnerPlan &op = hp.owner;
+    op = OwnerPlan{};
+    if (nb <= 0 || 2 * E > int64_t(INT32_MAX)) return;
+
+    // owner of a cell: the smallest block id among its edges' blocks; and the
+    // edges around a cell, ascending, each as 2 * edge + slot of the cell
+    std::vector<int32_t> owner(C, -1), own_off(nb + 1, 0), inc;
+    std::vector<uint8_t> deg(C);
+    for (op.quads = 1;; ++op.quads) {
+        const int32_t D = 4 * op.quads;
+        bool full = false;
+        inc.resize(size_t(C) * D);
+        for (int32_t b = 0; b < nb && !full; ++b)
+            for (int64_t i = 2 * int64_t(hp.blk_off[b]); i < 2 * int64_t(hp.blk_off[b + 1]); ++i) {
+                const int32_t c = mc.table[i];
+                if (owner[c] < 0) {
+                    owner[c] = b;
+                    own_off[b + 1]++;
+                }
+                if (deg[c] == D) {
+                    full = true;
+                    break;
+                }
+                inc[size_t(c) * D + deg[c]++] = int32_t(i);
+            }
+        if (!full) break;
+        if (op.quads == MAX_SIDE_QUADS) {
+            op = OwnerPlan{};
+            return;
+        }
+        std::fill(owner.begin(), owner.end(), -1);
+        std::fill(own_off.begin(), own_off.end(), 0);
+        std::fill(deg.begin(), deg.end(), 0);
+    }
+    for (int32_t b = 0; b < nb; ++b) own_off[b + 1] += own_off[b];
+    std::vector<int32_t> own(own_off[nb]);
+    {
+        std::vector<int32_t> fill(own_off.begin(), own_off.end() - 1);
+        for (int64_t c = 0; c < C; ++c)
+            if (owner[c] >= 0) own[fill[owner[c]]++] = int32_t(c);
+    }
+
+    // Consecutive workgroups go to the 8 XCDs in turn, each with its own L2,
+    // so neighbouring blocks, which stage each other's border cells, are
+    // dealt 8 apart: one eighth of the blocks to each XCD where the sweep's
+    // data stay in the 256 MB last-level cache (1200x600 cells: 19.2 us, in
+    // windows 19.6, in plain order 22.7), in windows where they stream from
+    // memory (2400x1200: 73.1 us, in eighths 76.4, in plain order 76.4).
+    const int64_t w = ea.dtype == UM_F64 ? 8 : 4;
+    const int64_t bytes = C * (5 * w + 32 + 12) + N * 2 * w;
+    const std::vector<int32_t> order =
+        o.xcd_groups > 1 ? interleaved_blocks(nb, o.xcd_groups)
+        : bytes > 256000000 ? windowed_blocks(nb) : interleaved_blocks(nb, 8);
+    std::vector<int32_t> pos_of(nb);
+    op.rec.resize(nb);
+    int64_t rows = 0;
+    for (int32_t k = 0; k < nb; ++k) {
+        pos_of[order[k]] = k;
+        op.rec[k].word_off = int32_t(rows);
+        op.rec[k].n_own = own_off[order[k] + 1] - own_off[order[k]];
+        rows += op.rec[k].n_own;
+        op.n_own_max = std::max(op.n_own_max, op.rec[k].n_own);
+    }
+    std::vector<std::vector<int32_t>> items(nb);
+    enum Result { OK = 0, NO_RING = 1, TOO_LARGE = 2 };
+    const int32_t D = 4 * op.quads;
+    // the records, listed ids and side words of blocks [b0, b1)
+    auto plan_range = [&](int32_t b0, int32_t b1, bool ring) -> Result {
+        // staged position + 1 of a point; 0 elsewhere, so that a thread only
+        // touches its own blocks' part of the arrays
+        const std::unique_ptr<uint16_t, void (*)(void *)> cm(zeroed(C), std::free),
+            nm(zeroed(N), std::free);
+        uint16_t *const cpos = cm.get(), *const npos = nm.get();
+        std::vector<int32_t> cells, nodes;
+        Side s[4 * MAX_SIDE_QUADS], g[4];
+        uint32_t corner[4];
+        for (int32_t b = b0; b < b1; ++b) {
+            const int32_t k = pos_of[b];
+            OwnRec &r = op.rec[k];
+            cells.assign(own.begin() + own_off[b], own.begin() + own_off[b + 1]);
+            nodes.clear();
+            for (int32_t c : cells) cpos[c] = 1;
+            for (int32_t i = 0; i < r.n_own; ++i)
+                for (int32_t a = 0; a < deg[cells[i]]; ++a) {
+                    const int64_t here = inc[size_t(cells[i]) * D + a], there = here ^ 1;
+                    const int32_t h = mc.table[there];
+                    if (!cpos[h]) {
+                        cpos[h] = 1;
+                        cells.push_back(h);
+                    }
+                    for (int64_t t : {here, there})
+                        if (!npos[mn.table[t]]) {
+                            npos[mn.table[t]] = 1;
+                            nodes.push_back(mn.table[t]);
+                        }
+                }
+            std::sort(cells.begin() + r.n_own, cells.end());
+            std::sort(nodes.begin(), nodes.end());
+            r.nc = int32_t(cells.size());
+            r.nn = int32_t(nodes.size());
+            if (r.nc > MAX_OWNER_POINTS || r.nn > MAX_OWNER_POINTS) return TOO_LARGE;
+            const bool lists = o.explicit_lists != 0;
+            r.c_run = lists ? 0 : leading_run(cells, r.n_own);
+            r.n_run = lists ? 0 : longest_run_first(nodes);
+            r.c_start = r.n_own ? cells[0] : 0;
+            r.n_start = r.nn ? nodes[0] : 0;
+            for (int32_t i = 0; i < r.nc; ++i) cpos[cells[i]] = uint16_t(i + 1);
+            for (int32_t i = 0; i < r.nn; ++i) npos[nodes[i]] = uint16_t(i + 1);
+            for (int32_t i = 0; i < r.n_own; ++i) {
+                int32_t n = 0;
+                for (; n < deg[cells[i]]; ++n) {
+                    // the normal of (a, b) points out of the edge's cell 0
+                    const int64_t here = inc[size_t(cells[i]) * D + n], there = here ^ 1;
+                    s[n] = Side{cpos[mc.table[there]] - 1u, npos[mn.table[here]] - 1u,
+                                npos[mn.table[there]] - 1u, uint32_t(here & 1)};
+                }
+                if (ring) {
+                    if (!arrange(s, n, g, corner)) return NO_RING;
+                    uint32_t *w = &op.words[3 * size_t(r.word_off) + i];
+                    w[0] = g[0].h | g[1].h << 10 | g[2].h << 20 | g[0].slot << 30 | g[1].slot << 31;
+                    w[r.n_own] =
+                        g[3].h | corner[0] << 10 | corner[1] << 20 | g[2].slot << 30 | g[3].slot << 31;
+                    w[2 * r.n_own] = corner[2] | corner[3] << 10;
+                } else {
+                    uint32_t *w = &op.words[(size_t(r.word_off) + i) * D];
+                    for (int32_t j = 0; j < D; ++j)
+                        w[j] = j < n ? s[j].h | s[j].a << 10 | s[j].b << 20 | s[j].slot << 30
+                                     : NO_SIDE;
+                }
+            }
+            // explicit ids: cells past the run, padded to a whole wavefront,
+            // then nodes past theirs
+            std::vector<int32_t> &it = items[k];
+            it.assign(cells.begin() + r.c_run, cells.end());
+            it.resize((it.size() + 63) / 64 * 64, 0);
+            r.node_item = int32_t(it.size());
+            it.insert(it.end(), nodes.begin() + r.n_run, nodes.end());
+            r.n_items = int32_t(it.size());
+            for (int32_t c : cells) cpos[c] = 0;
+            for (int32_t n : nodes) npos[n] = 0;
+        }
+        return OK;
+    };
+    Result res = op.quads == 1 ? OK : NO_RING;
+    for (bool ring : {true, false}) {
+        if (ring && res != OK) continue;
+        op.ring = ring;
+        op.words.assign(size_t(rows) * (ring ? 3 : D), 0u);
+        res = in_ranges(nb, E, [&](int32_t b0, int32_t b1) { return plan_range(b0, b1, ring); });
+        if (res != NO_RING) break;
+    }
+    for (const OwnRec &r : op.rec) {
+        op.id_stride = std::max(op.id_stride, r.n_items);
+        op.lds = std::max(op.lds, owner_lds_bytes(ea.dtype, r.nc, r.nn));
+    }
+    if (res != OK || op.lds > (o.lds_limit_bytes > 0 ? o.lds_limit_bytes : ctx.lds_limit)) {
+        op = OwnerPlan{};
+        return;
+    }
+    op.ids.assign(size_t(nb) * op.id_stride, 0);
+    for (int32_t k = 0; k < nb; ++k)
+        std::copy(items[k].begin(), items[k].end(), op.ids.begin() + size_t(k) * op.id_stride);
+    op.threads = std::max(64, (op.n_own_max + 63) / 64 * 64);  // a lane per owned cell
+    op.use = true;
+}
+
+}  // namespace um

@@ -42,7 +42,8 @@ UM_GLOBAL = -2
  UM_EXP_GLOBAL_COLOURS, UM_EXP_STAGED_OFFSETS_A, UM_EXP_STAGED_POINTS_A,
  UM_EXP_STAGED_OFFSETS_B, UM_EXP_STAGED_POINTS_B, UM_EXP_LOCAL_INDEX,
  UM_EXP_BLOCK_ORDER, UM_EXP_RUN_OFFSETS_A, UM_EXP_RUNS_A, UM_EXP_RUN_OFFSETS_B,
- UM_EXP_RUNS_B, UM_EXP_PRED_OFFSETS, UM_EXP_PREDS) = range(17)
+ UM_EXP_RUNS_B, UM_EXP_PRED_OFFSETS, UM_EXP_PREDS, UM_EXP_OWNER_RECORDS, UM_EXP_OWNER_IDS,
+ UM_EXP_OWNER_SIDES) = range(20)
 
 STATUS_NAMES = {0: "UM_OK", -1: "UM_ERR_ARG", -2: "UM_ERR_RANGE", -3: "UM_ERR_ARITY",
                 -4: "UM_ERR_COLOURS", -5: "UM_ERR_LDS", -6: "UM_ERR_HIP", -7: "UM_ERR_STATE",

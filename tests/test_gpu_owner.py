@@ -1,0 +1,93 @@
+"""GPU parity of the owner kernel (dataflow plans without waits) against the
+CPU oracle, at the forms its plans take: cells whose sides close a ring and
+cells of any other shape with up to eight sides, runs and listed ids, both
+layouts and storage types, one and many wavefronts per block.
+
+Bars: relative L2 1e-12 in binary64 (sums of at most 8 fluxes of about 30
+operations: 1e-15 from rounding), 1e-6 in binary32 storage against the
+oracle's binary32 evaluation (ulp 6e-8 over the same operations)."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+from meshgen import quad_mesh  # noqa: E402
+from oracle import native  # noqa: E402
+from paper_1802_03749_amd import umesh as U  # noqa: E402
+from paper_1802_03749_amd.edgeloop import EdgeFluxLoop  # noqa: E402
+
+
+def rel_l2(a, b):
+    a = np.asarray(a, np.longdouble); b = np.asarray(b, np.longdouble)
+    return float(np.sqrt(((a - b) ** 2).sum()) / np.sqrt((b ** 2).sum()))
+
+
+def random_cells(C, sides, seed):
+    """C cells of at most `sides` sides joined at random: no rings."""
+    rng = np.random.default_rng(seed)
+    ends = rng.permutation(np.repeat(np.arange(C), sides))[:C * sides // 2 * 2].reshape(-1, 2)
+    e2c = ends[ends[:, 0] != ends[:, 1]].astype(np.int32)
+    N = 3 * C
+    rho, p = rng.uniform(0.9, 1.1, C), rng.uniform(0.9, 1.1, C)
+    u, v = rng.uniform(-0.2, 0.2, (2, C))
+    q = np.stack([rho, rho * u, rho * v, p / 0.4 + 0.5 * rho * (u * u + v * v)], 1)
+    return (rng.uniform(-1, 1, (N, 2)), q, rng.uniform(1, 2, C),
+            rng.integers(0, N, e2c.shape).astype(np.int32), e2c)
+
+
+def check(mesh, dtype, layout, **kw):
+    x, q, adt, e2n, e2c = mesh
+    L = EdgeFluxLoop(x, q, adt, e2n, e2c, device=0, layout=layout, dtype=dtype, **kw.pop("loop"))
+    p = L.plan("hier", L.part_block_size or kw.pop("S"), schedule="dataflow",
+               gather="lds_dma" if layout == "aos" else "registers", **kw)
+    assert L.export(p, U.UM_EXP_OWNER_RECORDS).size
+    sides = L.export(p, U.UM_EXP_OWNER_SIDES)
+    for k in (1, 2):
+        L.run(p)
+    torch.cuda.synchronize()
+    if dtype == "f64":
+        assert rel_l2(L.res_user(), 2 * native.edge_loop(e2n, e2c, x, q, adt)) <= 1e-12
+    else:
+        r32, _ = native.edge_loop_f32(e2n, e2c, x, q, adt)
+        assert rel_l2(L.res_user(), 2 * r32) <= 1e-6
+    n = int(L.export(p, U.UM_EXP_OWNER_RECORDS).reshape(-1, 10)[:, 1].sum())
+    L.close()
+    return sides.size // (4 * n)
+
+
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+@pytest.mark.parametrize("layout", ["aos", "soa"])
+@pytest.mark.parametrize("nx,ny,S,points,explicit", [
+    (130, 67, 64, 2, False), (130, 67, 512, 0, False), (63, 64, 1024, 1, True),
+    (2, 1, 64, 2, False), (9, 200, 256, 3, False)])
+def test_ring_cells(nx, ny, S, points, explicit, layout, dtype):
+    m = quad_mesh(nx, ny, seed=6)
+    assert check((m.x, m.q, m.adt, m.e2n, m.e2c), dtype, layout, explicit_lists=explicit,
+                 loop=dict(order="rcm+partition", block_size=S, point_reorder=points)) == 4
+
+
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+@pytest.mark.parametrize("layout", ["aos", "soa"])
+@pytest.mark.parametrize("sides", [3, 4, 5, 8])
+def test_other_cells(sides, layout, dtype):
+    mesh = random_cells(90, sides, seed=sides)
+    assert check(mesh, dtype, layout, S=64, loop=dict(order="none")) == (4 if sides <= 4 else 8)
+
+
+def test_non_finite_states_stay_with_their_neighbours():
+    """An infinite or NaN state reaches the residuals of its own cell and of
+    the cells around it, as in the waiting kernel, and no other."""
+    m = quad_mesh(40, 30, seed=2)
+    q = m.q.copy()
+    q[100, 3], q[500, 1] = np.inf, np.nan
+    out = []
+    for gather in ("lds_dma", "registers"):
+        L = EdgeFluxLoop(m.x, q, m.adt, m.e2n, m.e2c, device=0, block_size=128)
+        L.run(L.plan("hier", 128, schedule="dataflow", gather=gather))
+        torch.cuda.synchronize()
+        out.append(L.res_user())
+        L.close()
+    assert np.array_equal(np.isfinite(out[0]), np.isfinite(out[1]))
+    fine = np.isfinite(out[0])
+    assert 0 < (~fine).sum() <= 40 and rel_l2(out[0][fine], out[1][fine]) <= 1e-12

@@ -1,0 +1,110 @@
+"""Host-side checks of the owner kernel's plans (no GPU): decoded from the
+exported records, every staged position is in range, every cell with an
+interior edge is owned by exactly one block, and an owned cell's sides are
+exactly the edges around it, with the normals pointing out."""
+import numpy as np
+import pytest
+
+from meshgen import quad_mesh
+from paper_1802_03749_amd import umesh as U
+from paper_1802_03749_amd.edgeloop import EdgeFluxLoop
+
+
+def tiles(m, tx, ty):
+    nat = m.cell_nat[m.e2c[:, 1]]
+    i, j = nat % m.nx, nat // m.nx
+    return ((j // ty) * ((m.nx + tx - 1) // tx) + i // tx).astype(np.int32)
+
+
+def decode(L, p):
+    """Per owned cell, in plan order: (cell, [(neighbour, a, b), ...])."""
+    rec = L.export(p, U.UM_EXP_OWNER_RECORDS).reshape(-1, 10)
+    ids = L.export(p, U.UM_EXP_OWNER_IDS).reshape(rec.shape[0], -1)
+    rows = int(rec[:, 1].sum())
+    sides = L.export(p, U.UM_EXP_OWNER_SIDES).reshape(rows, -1, 4)
+    out, row = [], 0
+    for r, it in zip(rec, ids):
+        word_off, n_own, nc, nn, c0, c_run, n0, n_run, node_item, n_items = r
+        assert word_off == row and c_run <= n_own <= nc <= 1023 and n_run <= nn <= 1023
+        assert node_item % 64 == 0 and node_item >= nc - c_run
+        assert n_items == node_item + nn - n_run <= ids.shape[1]
+        cells = np.concatenate([np.arange(c0, c0 + c_run), it[:nc - c_run]])
+        nodes = np.concatenate([np.arange(n0, n0 + n_run), it[node_item:n_items]])
+        assert cells.size == np.unique(cells).size == nc
+        assert nodes.size == np.unique(nodes).size == nn
+        assert nc == 0 or (cells.min() >= 0 and cells.max() < L.C)
+        assert nn == 0 or (nodes.min() >= 0 and nodes.max() < L.N)
+        for i in range(n_own):
+            s = sides[row + i]
+            s = s[s[:, 0] >= 0]
+            assert s.min(initial=0) >= 0
+            assert s[:, 0].max(initial=0) < nc and s[:, 1:3].max(initial=0) < nn
+            out.append((int(cells[i]), sorted((int(cells[h]), int(nodes[a]), int(nodes[b]), int(t))
+                                              for h, a, b, t in s)))
+        row += n_own
+    assert row == rows
+    return out
+
+
+@pytest.mark.parametrize("points", [0, 1, 2])
+@pytest.mark.parametrize("order,S,layout,explicit", [
+    ("rcm+partition", 512, "aos", False), ("partition", 64, "soa", False),
+    ("rcm+user", 256, "aos", False), ("rcm", 100, "aos", True), ("none", 256, "soa", False),
+    ("rcm+partition", 128, "aos", True)])
+@pytest.mark.parametrize("nx,ny", [(61, 37), (5, 3), (2, 1)])
+def test_owned_cells_and_their_sides(nx, ny, order, S, layout, explicit, points):
+    m = quad_mesh(nx, ny, seed=4)
+    L = EdgeFluxLoop(m.x, m.q, m.adt, m.e2n, m.e2c, device=-1, order=order, block_size=S,
+                     point_reorder=points, layout=layout, edge_blocks=tiles(m, 16, 8))
+    p = L.plan("hier", S, schedule="dataflow", elems_per_thread=2, explicit_lists=explicit,
+               gather="lds_dma" if layout == "aos" else "registers")
+    e2c, e2n = L.current_map("e2c"), L.current_map("e2n")
+    want = {}
+    for (l, r), (a, b) in zip(e2c.tolist(), e2n.tolist()):
+        want.setdefault(l, []).append((r, a, b, 0))
+        want.setdefault(r, []).append((l, b, a, 1))
+    try:
+        got = decode(L, p)
+    except U.UmeshError as e:
+        # a random order spreads a block over more cells than it may stage
+        assert e.status == U.UM_ERR_STATE and order == "none"
+        return
+    assert len(got) == len(want) and dict(got) == {c: sorted(s) for c, s in want.items()}
+    L.close()
+
+
+def test_edge_between_a_cell_and_itself():
+    """Both slots of such an edge are sides of the cell, with opposite
+    normals."""
+    e2c = np.array([[0, 1], [1, 1]], np.int32)
+    e2n = np.array([[0, 1], [2, 3]], np.int32)
+    L = EdgeFluxLoop(np.random.default_rng(0).uniform(size=(4, 2)), np.ones((2, 4)), np.ones(2),
+                     e2n, e2c, device=-1, order="none")
+    p = L.plan("hier", 64, schedule="dataflow", gather="lds_dma")
+    assert dict(decode(L, p)) == {0: [(1, 0, 1, 0)], 1: [(0, 1, 0, 1), (1, 2, 3, 0), (1, 3, 2, 1)]}
+    L.close()
+
+
+def test_plans_without_an_owner_kernel():
+    """The register gather on AoS data and cells with more than eight sides
+    keep the waiting kernels."""
+    m = quad_mesh(30, 20, seed=1)
+    L = EdgeFluxLoop(m.x, m.q, m.adt, m.e2n, m.e2c, device=-1)
+    for kw in (dict(schedule="dataflow"), dict()):
+        with pytest.raises(U.UmeshError):
+            L.export(L.plan("hier", 512, **kw), U.UM_EXP_OWNER_RECORDS)
+    L.close()
+    for arms, owned in ((8, True), (9, False)):
+        # a star: one cell with `arms` neighbours
+        e2c = np.stack([np.zeros(arms, np.int32), np.arange(1, arms + 1, dtype=np.int32)], 1)
+        x = np.random.default_rng(0).uniform(size=(2 * arms, 2))
+        L = EdgeFluxLoop(x, np.ones((arms + 1, 4)), np.ones(arms + 1),
+                         np.arange(2 * arms, dtype=np.int32).reshape(-1, 2), e2c, device=-1,
+                         order="none")
+        p = L.plan("hier", 64, schedule="dataflow", gather="lds_dma")
+        if owned:
+            assert sorted(len(s) for _, s in decode(L, p)) == [1] * arms + [arms]
+        else:
+            with pytest.raises(U.UmeshError):
+                L.export(p, U.UM_EXP_OWNER_RECORDS)
+        L.close()
