@@ -1104,8 +1104,8 @@ __global__ __launch_bounds__(1024) void owner_kernel(const OwnRec *__restrict__ 
         auto side = [&](int h, Real xa0, Real xa1, Real xb0, Real xb1, bool second) {
             Real qh[4], ah, f[4];
             state(h, qh, ah);
-            dev::lf2d_flux_out(xa0, xa1, xb0, xb1, q, own, qh, dev::flow_of(qh, gm1), a, ah, eps,
-                               second, f);
+            dev::lf2d_flux_out<LAYOUT == UM_SOA>(xa0, xa1, xb0, xb1, q, own, qh,
+                                                 dev::flow_of(qh, gm1), a, ah, eps, second, f);
 #pragma unroll
             for (int c = 0; c < 4; ++c) r[c] += double(f[c]);
         };
