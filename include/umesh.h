@@ -122,13 +122,13 @@ typedef enum { UM_BCOL_FIRST_FIT = 0, UM_BCOL_RECOLOUR = 1, UM_BCOL_MIN = 2 } um
  * completed (all flags advance together), so the launch needs no host-side
  * counter and may be captured in a HIP graph and replayed.  Supported for STAGE_ALL with one or two
  * elements per lane; a plan must not execute concurrently with itself.
- * Edge-loop plans with the LDS-DMA gather or SoA data need no order between
- * blocks where no cell has more than 8 edges and no block stages more than
- * 1023 cells or nodes: they run the owner kernel, in which each cell is
- * incremented by one of its blocks only (the first that touches it), which
- * evaluates all edges around it, those on its border too.  Such a launch has
- * no waits, no flags and no colour rounds; its results are reproducible bit
- * for bit in every um_tcmode.  The block and thread colours, the launch
+ * Plans of the hex loop, and of the edge loop with the LDS-DMA gather or SoA
+ * data, need no order between blocks where no cell has more than 8 edges (no
+ * node more than 16 elements), no block stages more than 1023 points of a
+ * set and the hex loop has at most 2,000,000 elements: they run the owner kernels, in which each point is incremented by
+ * one of its blocks only, which evaluates all elements around it, those on
+ * its border too.  Such a launch has no waits, no flags and no colour
+ * rounds; its results are reproducible bit for bit in every um_tcmode.  The block and thread colours, the launch
  * order by colour and the statistics below describe the plan's blocks all
  * the same. */
 typedef enum { UM_SCHED_COLOUR_LAUNCHES = 0, UM_SCHED_DATAFLOW = 1 } um_schedule;
@@ -418,7 +418,11 @@ typedef enum {
                                    order of their addition), the
                                    staged positions of the neighbour and of the two
                                    nodes, and the cell's slot in the edge; -1 for a
-                                   missing side                                      */
+                                   missing side.  Hex loop: int32[elements][8][2]
+                                   (records: nodes are owned, "staged nodes" counts
+                                   elements): staged position of each corner and, if
+                                   that node is owned, the element's place in its sum;
+                                   then int32[owned nodes]: places of each sum       */
 } um_export_field;
 
 /* ---------------------------------------------------------------- context */

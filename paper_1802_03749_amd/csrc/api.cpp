@@ -105,9 +105,10 @@ T *upload(const std::vector<T> &v, int64_t &bytes) {
 }
 
 void free_device_plan(Plan &p) {
-    void *bufs[16] = {p.dp.emap,  p.dp.binfo, p.dp.stg_c,    p.dp.stg_n, p.dp.loc,
+    void *bufs[17] = {p.dp.emap,  p.dp.binfo, p.dp.stg_c,    p.dp.stg_n, p.dp.loc,
                       p.dp.crun,  p.dp.nrun,  p.dp.pred_off, p.dp.preds, p.dp.frec,
-                      p.dp.flags, p.dp.err,   p.dp.partials, p.dp.own_rec, p.dp.own_ids, p.dp.own_words};
+                      p.dp.flags, p.dp.err,   p.dp.partials, p.dp.own_rec, p.dp.own_ids,
+                      p.dp.own_words, p.dp.own_counts};
     for (void *b : bufs)
         if (b) hipFree(b);
     p.dp = DevicePlan{};
@@ -272,6 +273,13 @@ LaunchArgs launch_args_hex(Plan &p, const double *params, int32_t nparams, void 
     la.flags = p.dp.flags;
     la.err = p.dp.err;
     la.wait_ticks = p.wait_ticks;
+    la.own_rec = p.dp.own_rec;
+    la.own_ids = p.dp.own_ids;
+    la.own_words = p.dp.own_words;
+    la.own_counts = p.dp.own_counts;
+    la.own_quads = p.hp.owner.quads;
+    la.own_stride = p.hp.owner.id_stride;
+    la.own_threads = p.hp.owner.threads;
     return la;
 }
 
@@ -665,6 +673,8 @@ um_status um_plan_build(um_ctx ctx, int32_t kernel, const um_arg *args, int32_t 
                     fail(UM_ERR_UNSUPPORTED, "LDS-DMA gather: edge flux loop only");
                 p->ha = check_hex_args(c, args, nargs, iter_set);
                 build_host_plan_hex(c, p->ha, iter_set, o, p->hp);
+                if (p->hp.strategy == UM_STRAT_HIER && p->hp.schedule == UM_SCHED_DATAFLOW)
+                    build_owner_plan_hex(c, p->ha, o, p->hp);
             }
             if (c.device >= 0) {
                 DeviceGuard g(c.device);
@@ -673,6 +683,7 @@ um_status um_plan_build(um_ctx ctx, int32_t kernel, const um_arg *args, int32_t 
                 p->dp.own_rec = upload(p->hp.owner.rec, bytes);
                 p->dp.own_ids = upload(p->hp.owner.ids, bytes);
                 p->dp.own_words = upload(p->hp.owner.words, bytes);
+                p->dp.own_counts = upload(p->hp.owner.counts, bytes);
                 p->dp.emap = upload(p->hp.emap, bytes);
                 if (!own) {
                     p->dp.binfo = upload(p->hp.binfo, bytes);
@@ -866,6 +877,15 @@ um_status um_plan_export(um_plan plan, int32_t field, int32_t *host_out, int64_t
             break;
         case UM_EXP_OWNER_SIDES:
             if (!hp.owner.use) fail(UM_ERR_STATE, "not a plan of the owner kernel");
+            if (p.kernel == UM_K_HEX_HOURGLASS_3D) {
+                for (size_t i = 0; i < hp.owner.words.size(); i += 4)
+                    for (int a = 0; a < 8; ++a) {
+                        tmp.push_back(int32_t((hp.owner.words[i + a / 3] >> (10 * (a % 3))) & 0x3FFu));
+                        tmp.push_back(int32_t((hp.owner.words[i + 3] >> (4 * a)) & 0xFu));
+                    }
+                for (uint8_t n : hp.owner.counts) tmp.push_back(n);
+                break;
+            }
             for (const OwnRec &r : hp.owner.rec)
                 for (int32_t i = 0; i < r.n_own; ++i) {
                     auto side = [&](uint32_t h, uint32_t a, uint32_t b, uint32_t slot, bool there) {

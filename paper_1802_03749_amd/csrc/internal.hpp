@@ -161,7 +161,8 @@ struct OwnRec {
     int32_t n_own, nc, nn;     // owned cells, staged cells, staged nodes
     int32_t c_start, c_run, n_start, n_run;
     int32_t node_item, n_items;
-    int32_t pad[2];
+    int32_t own_off;           // hex: owned nodes of the earlier blocks
+    int32_t pad;
 };
 static_assert(sizeof(OwnRec) == 48, "OwnRec is 12 words");
 
@@ -174,17 +175,26 @@ static_assert(sizeof(OwnRec) == 48, "OwnRec is 12 words");
 //   h3 | c0 << 10 | c1 << 20 | slot2 << 30 | slot3 << 31,  c2 | c3 << 10
 // in three planes per block.  General form: 4 * quads words per cell, each
 // h | a << 10 | b << 20 | slot << 30, NO_SIDE for a missing side.
+// Hex loop: nodes are owned, nc counts the staged nodes and nn the evaluated
+// elements, word_off those of the earlier blocks.  An element's four words:
+// staged positions l0..l7 of 10 bits, three to a word, then four bits per
+// corner, the place of the element in the corner's node's sum (owned nodes
+// only, whose staged positions come first); counts holds how many places an
+// owned node's sum has.
+constexpr int32_t MAX_NODE_ELEMENTS = 16;
 constexpr uint32_t NO_SIDE = 0xFFFFFFFFu, NO_CELL = 0x3FFu;
 constexpr int32_t MAX_OWNER_POINTS = 1023;     // staged cells, and staged nodes
 constexpr int32_t MAX_SIDE_QUADS = 2;          // at most 8 sides per cell
 
 struct OwnerPlan {
     bool use = false, ring = false;
-    int32_t threads = 0, quads = 1, id_stride = 0, n_own_max = 0;
+    int32_t threads = 0, id_stride = 0, n_own_max = 0;
+    int32_t quads = 1;                         // hex: most elements around a node
     int64_t lds = 0;
     std::vector<OwnRec> rec;
     std::vector<int32_t> ids;                  // [n_blocks][id_stride]
     std::vector<uint32_t> words;               // side words, blocks in launch order
+    std::vector<uint8_t> counts;               // hex: elements per owned node
 };
 
 struct HostPlan {
@@ -226,6 +236,7 @@ void build_host_plan(const Ctx &ctx, const EdgeArgs &ea, int32_t iter_set,
                      const um_plan_opts &o, HostPlan &hp);
 // Fills hp.owner of a dataflow edge plan where its blocks allow it.
 void build_owner_plan(const Ctx &ctx, const EdgeArgs &ea, const um_plan_opts &o, HostPlan &hp);
+void build_owner_plan_hex(const Ctx &ctx, const HexArgs &ha, const um_plan_opts &o, HostPlan &hp);
 void build_host_plan_hex(const Ctx &ctx, const HexArgs &ha, int32_t iter_set,
                          const um_plan_opts &o, HostPlan &hp);
 
@@ -246,6 +257,7 @@ void build_host_plan_step(const Ctx &ctx, int32_t kernel, const StepArgs &sa, in
 int64_t lf2d_lds_bytes(int32_t staging, int32_t dtype, int64_t n_cells, int64_t n_nodes);
 int64_t owner_lds_bytes(int32_t dtype, int64_t n_cells, int64_t n_nodes);
 int64_t hex_lds_bytes(int64_t n_nodes, bool dataflow);
+int64_t hex_owner_lds_bytes(int64_t n_nodes, int64_t n_own, int32_t places);
 
 // ----------------------------------------------------------------- device
 struct DevicePlan {
@@ -262,6 +274,7 @@ struct DevicePlan {
     OwnRec *own_rec = nullptr;                      // owner kernel
     int32_t *own_ids = nullptr;
     uint32_t *own_words = nullptr;
+    uint8_t *own_counts = nullptr;
     double *partials = nullptr;                     // UPDATE: one sum per workgroup
     int64_t bytes = 0;
 };

@@ -361,6 +361,175 @@ __global__ __launch_bounds__(1024) void hex_flow_kernel(
     if (tid == 0) __hip_atomic_store(flags + pos, epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// One component of an element's forces on its corners from its corners'
+// velocities v, c = -kappa h: the four modes m_i = sum_a G_i[a] v[a], then
+// f[a] = c sum_i G_i[a] m_i (hg_term has the signs).  The base vectors are
+// equal on opposite corners except the fourth, which changes sign there, so
+// sums and differences of opposite corners take 37 operations instead of 60.
+__device__ __forceinline__ void hex_component(const double v[8], double c, double f[8]) {
+    const double s0 = v[0] + v[6], s1 = v[1] + v[7], s2 = v[2] + v[4], s3 = v[3] + v[5];
+    const double a = s0 - s2, b = s1 - s3;
+    const double m1 = c * (a + b), m2 = c * (a - b), m3 = c * ((s0 + s2) - (s1 + s3));
+    const double m4 = c * (((v[6] - v[0]) + (v[1] - v[7])) + ((v[4] - v[2]) + (v[3] - v[5])));
+    const double p = m2 + m3, q = m2 - m3;
+    const double t0 = m1 + p, t1 = m1 - p, t2 = -(m1 + q), t3 = q - m1;
+    f[0] = t0 - m4; f[6] = t0 + m4;
+    f[1] = t1 + m4; f[7] = t1 - m4;
+    f[2] = t2 - m4; f[4] = t2 + m4;
+    f[3] = t3 + m4; f[5] = t3 - m4;
+}
+
+// Owner kernel (planner_owner.cpp): a block owns nodes and evaluates every
+// element around them, a lane per element, those on its border as their other
+// blocks do.  The elements' contributions to one force component of the owned
+// nodes go to LDS, each to a place of its own, and a lane per owned node adds
+// them in a fixed order: no waits between blocks, no colours, no atomics.
+// Components are taken one after another, so that the contributions (over
+// the staged x, which only the element lengths need) take 8 doubles per node.
+// At 96^3 the gather alone takes 26 us (132 MB counted, the memory's rate),
+// the evaluation alone 28 (LDS busy for 16 us, the vector units for 13), the
+// sweep 34.5; the waiting kernel 49.9.  At 33^3 (SoA), where a chain of eight
+// colours was everything, 28.3 -> 6.9 us.  Taking three blocks to a compute
+// unit instead of four costs 2 %; staging the nodes in the elements' order, or
+// the largest blocks' sums in several passes to fit a fourth block, gained
+// nothing.
+template <int LAYOUT>
+__global__ __launch_bounds__(1024) void hex_owner_kernel(
+    const OwnRec *__restrict__ recs, const int32_t *__restrict__ ids, int32_t id_stride,
+    const uint4 *__restrict__ words, const uint8_t *__restrict__ counts, int32_t places,
+    HexDats d, double kappa) {
+    extern __shared__ double lds[];
+    const int32_t pos = int32_t(blockIdx.x);
+    const int tid = int(threadIdx.x), T = int(blockDim.x);
+    const int32_t *__restrict__ my_ids = ids + int64_t(pos) * id_stride;
+    // this lane's listed id, together with the record
+    const int32_t id0 = tid < id_stride ? my_ids[tid] : 0;
+    const OwnRec &rec = recs[pos];
+    const int n_own = rec.n_own, nn = rec.nc, ne = rec.nn;
+    const int c_run = rec.c_run, n_items = rec.n_items;
+    const int32_t c_start = rec.c_start;
+    double *s_v = lds;           // [nn][3]
+    double *s_x = s_v + 3 * nn;  // [nn][3]
+    double *s_f = s_x;           // [places][n_own] and 32 unused, once the lengths are known
+
+    // all loads of the block's first pass before any of them is used: the
+    // listed nodes, the run of consecutive nodes (AoS: double by double, at
+    // most 3 per lane since there is a lane per owned node), the element's
+    // words, the owned node's force
+    double xi[3], vi[3], xr[3], vr[3];
+    if (tid < n_items) {
+        load3<LAYOUT>(d.x, d.N, id0, xi);
+        load3<LAYOUT>(d.v, d.N, id0, vi);
+    }
+    if constexpr (LAYOUT == UM_AOS) {
+#pragma unroll
+        for (int i = 0; i < 3; ++i)
+            if (tid + i * T < 3 * c_run) {
+                xr[i] = d.x[3 * int64_t(c_start) + tid + i * T];
+                vr[i] = d.v[3 * int64_t(c_start) + tid + i * T];
+            }
+    } else if (tid < c_run) {
+        load3<LAYOUT>(d.x, d.N, c_start + tid, xr);
+        load3<LAYOUT>(d.v, d.N, c_start + tid, vr);
+    }
+    uint4 w = make_uint4(0, 0, 0, 0);
+    if (tid < ne) w = words[rec.word_off + tid];
+    int n_places = 0;
+    int32_t own_id = 0;
+    double f[3] = {0.0, 0.0, 0.0};
+    if (tid < n_own) {
+        own_id = tid < c_run ? c_start + tid : my_ids[tid - c_run];
+        n_places = counts[rec.own_off + tid];
+        load3<LAYOUT>(d.force, d.N, own_id, f);
+    }
+    if (tid < n_items)
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            s_x[3 * (c_run + tid) + k] = xi[k];
+            s_v[3 * (c_run + tid) + k] = vi[k];
+        }
+    if constexpr (LAYOUT == UM_AOS) {
+#pragma unroll
+        for (int i = 0; i < 3; ++i)
+            if (tid + i * T < 3 * c_run) {
+                s_x[tid + i * T] = xr[i];
+                s_v[tid + i * T] = vr[i];
+            }
+    } else if (tid < c_run) {
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            s_x[3 * tid + k] = xr[k];
+            s_v[3 * tid + k] = vr[k];
+        }
+    }
+    for (int j = tid + T; j < n_items; j += T) {
+        const int32_t g = my_ids[j];
+        load3<LAYOUT>(d.x, d.N, g, xi);
+        load3<LAYOUT>(d.v, d.N, g, vi);
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            s_x[3 * (c_run + j) + k] = xi[k];
+            s_v[3 * (c_run + j) + k] = vi[k];
+        }
+    }
+    __syncthreads();
+
+    // the element's corners, and where its contributions to them go: a place
+    // of an owned node's sum, or the unused words behind
+    int l[8], at[8];
+#pragma unroll
+    for (int a = 0; a < 8; ++a) {
+        const uint32_t v = a < 3 ? w.x : a < 6 ? w.y : w.z;
+        l[a] = int((v >> (10 * (a % 3))) & 0x3FFu);
+        at[a] = l[a] < n_own ? int((w.w >> (4 * a)) & 0xFu) * n_own + l[a]
+                             : places * n_own + (tid & 31);
+        l[a] *= 3;
+    }
+    double c = 0.0;
+    if (tid < ne) {
+        const double dx = s_x[l[6]] - s_x[l[0]];
+        const double dy = s_x[l[6] + 1] - s_x[l[0] + 1];
+        const double dz = s_x[l[6] + 2] - s_x[l[0] + 2];
+        c = -kappa * sqrt(dx * dx + dy * dy + dz * dz);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        if (tid < ne) {
+            double v[8], g[8];
+#pragma unroll
+            for (int a = 0; a < 8; ++a) v[a] = s_v[l[a] + k];
+            hex_component(v, c, g);
+#pragma unroll
+            for (int a = 0; a < 8; ++a) s_f[at[a]] = g[a];
+        }
+        __syncthreads();
+        if (tid < n_own) {
+            double s = 0.0, g[8];
+            if (__all(n_places == 8)) {  // most wavefronts
+#pragma unroll
+                for (int p = 0; p < 8; ++p) g[p] = s_f[p * n_own + tid];
+#pragma unroll
+                for (int p = 0; p < 8; ++p) s += g[p];
+            } else {
+                for (int p0 = 0; p0 < places; p0 += 8) {
+#pragma unroll
+                    for (int p = 0; p < 8; ++p)
+                        g[p] = p0 + p < n_places ? s_f[(p0 + p) * n_own + tid] : 0.0;
+#pragma unroll
+                    for (int p = 0; p < 8; ++p) s += g[p];
+                }
+            }
+            f[k] += s;
+        }
+        if (k < 2) __syncthreads();
+    }
+    if (tid < n_own) {
+#pragma unroll
+        for (int k = 0; k < 3; ++k) d.force[idx3<LAYOUT>(d.N, own_id, k)] = f[k];
+    }
+}
+
 template <int LAYOUT>
 __device__ __forceinline__ void gather_element(const HexDats &d, const int32_t *row,
                                                double xe[8][3], double ve[8][3]) {
@@ -446,6 +615,17 @@ hipError_t hex_launch_layout(const LaunchArgs &la, int which, int32_t begin, int
         hipLaunchKernelGGL(kern, dim3(end - begin), dim3(la.block_size), size_t(lds), la.stream,
                            la.binfo, la.stg_c, la.crun, reinterpret_cast<const uint4 *>(la.loc), d,
                            kappa, la.pred_off, la.preds, la.flags, la.err, la.wait_ticks);
+        return hipGetLastError();
+    }
+    if (which == LAUNCH_OWNER) {
+        clear_stale_error();
+        const hipError_t ea =
+            allow_lds(reinterpret_cast<const void *>(hex_owner_kernel<LAYOUT>), lds);
+        if (ea != hipSuccess) return ea;
+        hipLaunchKernelGGL((hex_owner_kernel<LAYOUT>), dim3(end - begin), dim3(la.own_threads),
+                           size_t(lds), la.stream, la.own_rec, la.own_ids, la.own_stride,
+                           reinterpret_cast<const uint4 *>(la.own_words), la.own_counts, la.own_quads, d,
+                           kappa);
         return hipGetLastError();
     }
     const int32_t n = end - begin;

@@ -37,7 +37,8 @@ struct LaunchArgs {
     const OwnRec *own_rec;    // owner kernel: per launch position
     const int32_t *own_ids;
     const uint32_t *own_words;
-    int32_t own_stride, own_threads, own_quads;  // quads 0: sides in ring form
+    const uint8_t *own_counts;
+    int32_t own_stride, own_threads, own_quads;  // quads 0: sides in ring form; hex: places
     uint64_t wait_ticks;   // DATAFLOW: longest wait for one neighbour (100 MHz ticks)
     double qinf[4];        // BOUNDARY_FLUX: far-field state
     double *partials;      // UPDATE: per-workgroup sums

@@ -18,6 +18,12 @@ int64_t hex_lds_bytes(int64_t nn, bool dataflow) {
     return nn * (9 * 8 + 4) + (dataflow ? 3 * 8 * (((nn + 15) & ~int64_t(15)) - nn) : 0);
 }
 
+int64_t hex_owner_lds_bytes(int64_t nn, int64_t n_own, int32_t places) {
+    // v, then x and, over it, one component's contributions per owned node
+    // (and 32 doubles for those to other nodes)
+    return 24 * nn + std::max(24 * nn, 8 * (n_own * places + 32));
+}
+
 int64_t lf2d_lds_bytes(int32_t staging, int32_t dtype, int64_t nc, int64_t nn) {
     const int64_t inc = nc * 4 * 8;  // FP64 increments (res preloaded)
     if (staging == UM_STAGE_INC_ONLY) return inc;

@@ -8,6 +8,7 @@
 #include <cstdint>
 #include <cstdlib>
 #include <exception>
+#include <initializer_list>
 #include <memory>
 #include <new>
 #include <thread>
@@ -72,6 +73,68 @@ int32_t longest_run_first(std::vector<int32_t> &v) {
     std::rotate(v.begin(), v.begin() + best, v.begin() + best + len);
     return int32_t(len);
 }
+
+// Consecutive workgroups go to the 8 XCDs in turn, each with its own L2, so
+// neighbouring blocks, which stage each other's border points, are dealt 8
+// apart: one eighth of the blocks to each XCD where the sweep's data stay in
+// the 256 MB last-level cache (edge loop, 1200x600 cells: 19.2 us, in windows
+// 19.6, in plain order 22.7), in windows where they stream from memory
+// (2400x1200: 73.1 us, in eighths 76.4, in plain order 76.4).
+std::vector<int32_t> launch_order(int32_t nb, const um_plan_opts &o, int64_t bytes) {
+    if (o.xcd_groups > 1) return interleaved_blocks(nb, o.xcd_groups);
+    return bytes > 256000000 ? windowed_blocks(nb) : interleaved_blocks(nb, 8);
+}
+
+// The owners of a map's points, and the elements around each point.
+struct Around {
+    int32_t D = 0;                       // incidences held per point
+    std::vector<int32_t> own_off, own;   // per block: its points, ascending
+    std::vector<int32_t> inc;            // [points][D]: arity * element + slot, ascending
+    std::vector<uint8_t> deg;            // how many of them
+
+    // Owner of a point: the first of the blocks that touch it or, where that
+    // leaves the blocks' points in fewer runs of consecutive ids, the last.
+    // False if a point has more incidences than the largest of `sizes`.
+    bool build(const Map &m, int64_t P, const std::vector<int32_t> &blk_off,
+               std::initializer_list<int32_t> sizes) {
+        const int32_t nb = int32_t(blk_off.size()) - 1;
+        const int64_t k = m.arity;
+        if (k * int64_t(blk_off[nb]) > int64_t(INT32_MAX)) return false;
+        std::vector<int32_t> first(P), last(P);
+        bool full = true;
+        for (auto size = sizes.begin(); full && size != sizes.end(); ++size) {
+            D = *size;
+            full = false;
+            inc.resize(size_t(P) * D);
+            deg.assign(P, 0);
+            std::fill(first.begin(), first.end(), -1);
+            for (int32_t b = 0; b < nb && !full; ++b)
+                for (int64_t i = k * blk_off[b]; i < k * blk_off[b + 1]; ++i) {
+                    const int32_t p = m.table[i];
+                    if (first[p] < 0) first[p] = b;
+                    last[p] = b;
+                    full = deg[p] == D;
+                    if (full) break;
+                    inc[size_t(p) * D + deg[p]++] = int32_t(i);
+                }
+        }
+        if (full) return false;
+        int64_t breaks = 0;
+        for (int64_t p = 1; p < P; ++p)
+            if (first[p] >= 0 && first[p - 1] >= 0)
+                breaks += (last[p] != last[p - 1]) - (first[p] != first[p - 1]);
+        const std::vector<int32_t> &owner = breaks < 0 ? last : first;
+        own_off.assign(nb + 1, 0);
+        for (int64_t p = 0; p < P; ++p)
+            if (first[p] >= 0) own_off[owner[p] + 1]++;
+        for (int32_t b = 0; b < nb; ++b) own_off[b + 1] += own_off[b];
+        own.resize(own_off[nb]);
+        std::vector<int32_t> fill(own_off.begin(), own_off.end() - 1);
+        for (int64_t p = 0; p < P; ++p)
+            if (first[p] >= 0) own[fill[owner[p]]++] = int32_t(p);
+        return true;
+    }
+};
 
 uint16_t *zeroed(int64_t n) {
     void *p = std::calloc(size_t(std::max<int64_t>(n, 1)), sizeof(uint16_t));
@@ -191,57 +254,16 @@ void build_owner_plan(const Ctx &ctx, const EdgeArgs &ea, const um_plan_opts &o,
     const int32_t nb = int32_t(hp.blk_off.size()) - 1;
     OwnerPlan &op = hp.owner;
     op = OwnerPlan{};
-    if (nb <= 0 || 2 * E > int64_t(INT32_MAX)) return;
+    if (nb <= 0) return;
 
-    // owner of a cell: the smallest block id among its edges' blocks; and the
-    // edges around a cell, ascending, each as 2 * edge + slot of the cell
-    std::vector<int32_t> owner(C, -1), own_off(nb + 1, 0), inc;
-    std::vector<uint8_t> deg(C);
-    for (op.quads = 1;; ++op.quads) {
-        const int32_t D = 4 * op.quads;
-        bool full = false;
-        inc.resize(size_t(C) * D);
-        for (int32_t b = 0; b < nb && !full; ++b)
-            for (int64_t i = 2 * int64_t(hp.blk_off[b]); i < 2 * int64_t(hp.blk_off[b + 1]); ++i) {
-                const int32_t c = mc.table[i];
-                if (owner[c] < 0) {
-                    owner[c] = b;
-                    own_off[b + 1]++;
-                }
-                if (deg[c] == D) {
-                    full = true;
-                    break;
-                }
-                inc[size_t(c) * D + deg[c]++] = int32_t(i);
-            }
-        if (!full) break;
-        if (op.quads == MAX_SIDE_QUADS) {
-            op = OwnerPlan{};
-            return;
-        }
-        std::fill(owner.begin(), owner.end(), -1);
-        std::fill(own_off.begin(), own_off.end(), 0);
-        std::fill(deg.begin(), deg.end(), 0);
-    }
-    for (int32_t b = 0; b < nb; ++b) own_off[b + 1] += own_off[b];
-    std::vector<int32_t> own(own_off[nb]);
-    {
-        std::vector<int32_t> fill(own_off.begin(), own_off.end() - 1);
-        for (int64_t c = 0; c < C; ++c)
-            if (owner[c] >= 0) own[fill[owner[c]]++] = int32_t(c);
-    }
+    Around ar;
+    if (!ar.build(mc, C, hp.blk_off, {4, 4 * MAX_SIDE_QUADS})) return;
+    op.quads = ar.D / 4;
+    const auto &[D, own_off, own, inc, deg] = ar;
 
-    // Consecutive workgroups go to the 8 XCDs in turn, each with its own L2,
-    // so neighbouring blocks, which stage each other's border cells, are
-    // dealt 8 apart: one eighth of the blocks to each XCD where the sweep's
-    // data stay in the 256 MB last-level cache (1200x600 cells: 19.2 us, in
-    // windows 19.6, in plain order 22.7), in windows where they stream from
-    // memory (2400x1200: 73.1 us, in eighths 76.4, in plain order 76.4).
     const int64_t w = ea.dtype == UM_F64 ? 8 : 4;
-    const int64_t bytes = C * (5 * w + 32 + 12) + N * 2 * w;
     const std::vector<int32_t> order =
-        o.xcd_groups > 1 ? interleaved_blocks(nb, o.xcd_groups)
-        : bytes > 256000000 ? windowed_blocks(nb) : interleaved_blocks(nb, 8);
+        launch_order(nb, o, C * (5 * w + 32 + 12) + N * 2 * w);
     std::vector<int32_t> pos_of(nb);
     op.rec.resize(nb);
     int64_t rows = 0;
@@ -254,7 +276,6 @@ void build_owner_plan(const Ctx &ctx, const EdgeArgs &ea, const um_plan_opts &o,
     }
     std::vector<std::vector<int32_t>> items(nb);
     enum Result { OK = 0, NO_RING = 1, TOO_LARGE = 2 };
-    const int32_t D = 4 * op.quads;
     // the records, listed ids and side words of blocks [b0, b1)
     auto plan_range = [&](int32_t b0, int32_t b1, bool ring) -> Result {
         // staged position + 1 of a point; 0 elsewhere, so that a thread only
@@ -352,6 +373,118 @@ void build_owner_plan(const Ctx &ctx, const EdgeArgs &ea, const um_plan_opts &o,
     for (int32_t k = 0; k < nb; ++k)
         std::copy(items[k].begin(), items[k].end(), op.ids.begin() + size_t(k) * op.id_stride);
     op.threads = std::max(64, (op.n_own_max + 63) / 64 * 64);  // a lane per owned cell
+    op.use = true;
+}
+
+// The same for the hex loop: nodes are owned, a block evaluates every element
+// around its nodes.
+void build_owner_plan_hex(const Ctx &ctx, const HexArgs &ha, const um_plan_opts &o,
+                          HostPlan &hp) {
+    const Map &m = ctx.maps[ha.map];
+    const int64_t N = ctx.sets[m.to].size, E = hp.n_elem;
+    const int32_t nb = int32_t(hp.blk_off.size()) - 1;
+    OwnerPlan &op = hp.owner;
+    op = OwnerPlan{};
+    // A brick of 8x8x4 elements evaluates 405 for its 256 nodes.  Up to about
+    // two million elements that costs less than waiting for eight block
+    // colours in turn; beyond, the chain is hidden and the extra evaluations
+    // are not.  One sweep, waiting -> owner kernel: 24^3 elements 22.5 -> 5.7
+    // us, 64^3 39.0 -> 11.9, 96^3 58.3 -> 34.5 (49.9 with MIN colouring), 120^3
+    // 80.9 -> 70.4, but 128^3 73.4 -> 75.5 and, with LDS atomics, 67.8 -> 75.6.
+    if (nb <= 0 || E > 2000000) return;
+    Around ar;
+    if (!ar.build(m, N, hp.blk_off, {8, MAX_NODE_ELEMENTS})) return;
+    const auto &[D, own_off, own, inc, deg] = ar;
+    for (uint8_t n : deg) op.quads = std::max<int32_t>(op.quads, n);
+
+    const std::vector<int32_t> order = launch_order(nb, o, N * 72 + E * 24);
+    std::vector<int32_t> pos_of(nb);
+    op.rec.resize(nb);
+    op.counts.reserve(own.size());
+    int64_t owned = 0;
+    for (int32_t k = 0; k < nb; ++k) {
+        const int32_t b = order[k];
+        pos_of[b] = k;
+        op.rec[k].own_off = int32_t(owned);
+        op.rec[k].n_own = own_off[b + 1] - own_off[b];
+        op.n_own_max = std::max(op.n_own_max, op.rec[k].n_own);
+        owned += op.rec[k].n_own;
+    }
+    op.counts.resize(owned);
+    std::vector<std::vector<int32_t>> items(nb);
+    std::vector<std::vector<uint32_t>> words(nb);
+    // the records, listed ids and elements of blocks [b0, b1): 0, or 1 if one
+    // of them is too large
+    auto plan_range = [&](int32_t b0, int32_t b1) -> int32_t {
+        const std::unique_ptr<uint16_t, void (*)(void *)> nm(zeroed(N), std::free);
+        uint16_t *const npos = nm.get();
+        std::vector<int32_t> nodes, elems;
+        std::vector<uint8_t> seen;
+        for (int32_t b = b0; b < b1; ++b) {
+            const int32_t k = pos_of[b];
+            OwnRec &r = op.rec[k];
+            nodes.assign(own.begin() + own_off[b], own.begin() + own_off[b + 1]);
+            elems.clear();
+            for (int32_t n : nodes)
+                for (int32_t a = 0; a < deg[n]; ++a) elems.push_back(inc[size_t(n) * D + a] / 8);
+            std::sort(elems.begin(), elems.end());
+            elems.erase(std::unique(elems.begin(), elems.end()), elems.end());
+            for (int32_t n : nodes) npos[n] = 1;
+            for (int32_t e : elems)
+                for (int a = 0; a < 8; ++a) {
+                    const int32_t n = m.table[8 * int64_t(e) + a];
+                    if (!npos[n]) {
+                        npos[n] = 1;
+                        nodes.push_back(n);
+                    }
+                }
+            std::sort(nodes.begin() + r.n_own, nodes.end());
+            r.nc = int32_t(nodes.size());
+            r.nn = int32_t(elems.size());
+            if (r.nc > MAX_OWNER_POINTS || r.nn > 1024) return 1;
+            r.c_run = o.explicit_lists != 0 ? 0 : leading_run(nodes, r.n_own);
+            r.c_start = r.n_own ? nodes[0] : 0;
+            for (int32_t i = 0; i < r.nc; ++i) npos[nodes[i]] = uint16_t(i + 1);
+            for (int32_t i = 0; i < r.n_own; ++i) op.counts[r.own_off + i] = deg[nodes[i]];
+            std::vector<uint32_t> &w = words[k];
+            w.assign(4 * size_t(r.nn), 0u);
+            seen.assign(r.n_own, 0);
+            for (int32_t i = 0; i < r.nn; ++i)
+                for (int a = 0; a < 8; ++a) {
+                    const uint32_t t = npos[m.table[8 * int64_t(elems[i]) + a]] - 1u;
+                    w[4 * i + a / 3] |= t << (10 * (a % 3));
+                    if (t < uint32_t(r.n_own)) w[4 * i + 3] |= uint32_t(seen[t]++) << (4 * a);
+                }
+            std::vector<int32_t> &it = items[k];
+            it.assign(nodes.begin() + r.c_run, nodes.end());
+            r.n_items = int32_t(it.size());
+            for (int32_t n : nodes) npos[n] = 0;
+        }
+        return 0;
+    };
+    const int32_t res = in_ranges(nb, 8 * E, plan_range);
+    int64_t rows = 0;
+    int32_t lanes = 64;
+    for (int32_t k = 0; k < nb; ++k) {
+        OwnRec &r = op.rec[k];
+        r.word_off = int32_t(rows);
+        rows += r.nn;
+        op.id_stride = std::max(op.id_stride, r.n_items);
+        op.lds = std::max(op.lds, hex_owner_lds_bytes(r.nc, r.n_own, op.quads));
+        lanes = std::max({lanes, r.nn, r.n_own});
+    }
+    op.threads = (lanes + 63) / 64 * 64;
+    if (res != 0 || op.threads > 1024 || rows > int64_t(INT32_MAX) ||
+        op.lds > (o.lds_limit_bytes > 0 ? o.lds_limit_bytes : ctx.lds_limit)) {
+        op = OwnerPlan{};
+        return;
+    }
+    op.words.reserve(4 * size_t(rows));
+    op.ids.assign(size_t(nb) * op.id_stride, 0);
+    for (int32_t k = 0; k < nb; ++k) {
+        op.words.insert(op.words.end(), words[k].begin(), words[k].end());
+        std::copy(items[k].begin(), items[k].end(), op.ids.begin() + size_t(k) * op.id_stride);
+    }
     op.use = true;
 }
 

@@ -1,7 +1,8 @@
-"""GPU parity of the owner kernel (dataflow plans without waits) against the
-CPU oracle, at the forms its plans take: cells whose sides close a ring and
-cells of any other shape with up to eight sides, runs and listed ids, both
-layouts and storage types, one and many wavefronts per block.
+"""GPU parity of the owner kernels (dataflow plans without waits) against the
+CPU oracle, at the forms their plans take.  Edge loop: cells whose sides close
+a ring and cells of any other shape with up to eight sides, runs and listed
+ids, both layouts and storage types, one and many wavefronts per block.  Hex
+loop: grids at several block sizes and nodes with up to sixteen elements.
 
 Bars: relative L2 1e-12 in binary64 (sums of at most 8 fluxes of about 30
 operations: 1e-15 from rounding), 1e-6 in binary32 storage against the
@@ -12,10 +13,11 @@ import pytest
 torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
 
-from meshgen import quad_mesh  # noqa: E402
+from meshgen import hex_mesh, quad_mesh  # noqa: E402
 from oracle import native  # noqa: E402
 from paper_1802_03749_amd import umesh as U  # noqa: E402
 from paper_1802_03749_amd.edgeloop import EdgeFluxLoop  # noqa: E402
+from paper_1802_03749_amd.hexloop import HexLoop  # noqa: E402
 
 
 def rel_l2(a, b):
@@ -73,6 +75,40 @@ def test_ring_cells(nx, ny, S, points, explicit, layout, dtype):
 def test_other_cells(sides, layout, dtype):
     mesh = random_cells(90, sides, seed=sides)
     assert check(mesh, dtype, layout, S=64, loop=dict(order="none")) == (4 if sides <= 4 else 8)
+
+
+def check_hex(x, v, e2n, layout, loop, S, **kw):
+    L = HexLoop(x, v, e2n, device=0, layout=layout, **loop)
+    p = L.plan("hier", S, schedule="dataflow", block_colouring="recolour", **kw)
+    assert L.export(p, U.UM_EXP_OWNER_RECORDS).size
+    for k in (1, 2):
+        L.run(p)
+    torch.cuda.synchronize()
+    assert rel_l2(L.force_user(), 2 * native.hex_loop(e2n, x, v)) <= 1e-12
+    L.close()
+
+
+@pytest.mark.parametrize("layout", ["aos", "soa"])
+@pytest.mark.parametrize("n,S,points,explicit", [(1, 64, 1, False), (9, 64, 3, False),
+                                                 (17, 256, 2, False), (17, 256, 0, True),
+                                                 (16, 512, 3, False), (23, 128, 1, False)])
+def test_hex(n, S, points, explicit, layout):
+    m = hex_mesh(n, seed=6)
+    check_hex(m.x, m.v, m.e2n, layout, dict(order="rcm+partition", block_size=S,
+                                            point_reorder=points), S, explicit_lists=explicit,
+              tcmode="lds_atomic" if n == 23 else "barrier")
+
+
+@pytest.mark.parametrize("layout", ["aos", "soa"])
+@pytest.mark.parametrize("around", [3, 9, 16])
+def test_hex_nodes_of_other_degrees(around, layout):
+    """Elements on random nodes, up to 16 around a node."""
+    rng = np.random.default_rng(around)
+    N = 160
+    e2n = rng.permutation(np.repeat(np.arange(N), around))[:N * around // 8 * 8]
+    e2n = e2n.reshape(-1, 8).astype(np.int32)
+    check_hex(rng.uniform(-1, 1, (N, 3)), rng.uniform(-1, 1, (N, 3)), e2n, layout,
+              dict(order="none"), 64)
 
 
 def test_non_finite_states_stay_with_their_neighbours():

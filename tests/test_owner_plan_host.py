@@ -5,9 +5,10 @@ exactly the edges around it, with the normals pointing out."""
 import numpy as np
 import pytest
 
-from meshgen import quad_mesh
+from meshgen import hex_mesh, quad_mesh
 from paper_1802_03749_amd import umesh as U
 from paper_1802_03749_amd.edgeloop import EdgeFluxLoop
+from paper_1802_03749_amd.hexloop import HexLoop
 
 
 def tiles(m, tx, ty):
@@ -108,3 +109,48 @@ def test_plans_without_an_owner_kernel():
             with pytest.raises(U.UmeshError):
                 L.export(p, U.UM_EXP_OWNER_RECORDS)
         L.close()
+
+
+@pytest.mark.parametrize("points", [0, 1, 3])
+@pytest.mark.parametrize("n,S,explicit", [(9, 256, False), (9, 64, True), (1, 64, False),
+                                          (12, 512, False), (2, 128, False)])
+def test_hex_owned_nodes_and_their_elements(n, S, explicit, points):
+    """Every node is owned once; its sum has one place for each element
+    around it, filled by that element's corner at the node."""
+    m = hex_mesh(n, seed=3)
+    L = HexLoop(m.x, m.v, m.e2n, device=-1, order="rcm+partition", block_size=S,
+                point_reorder=points)
+    p = L.plan("hier", S, schedule="dataflow", block_colouring="min", explicit_lists=explicit)
+    rec = L.export(p, U.UM_EXP_OWNER_RECORDS).reshape(-1, 10)
+    ids = L.export(p, U.UM_EXP_OWNER_IDS).reshape(rec.shape[0], -1)
+    ex = L.export(p, U.UM_EXP_OWNER_SIDES)
+    rows = int(rec[:, 3].sum())
+    corners, counts = ex[:16 * rows].reshape(rows, 8, 2), ex[16 * rows:]
+    e2n = L.current_map()
+    want = [[] for _ in range(L.N)]
+    for e, row in enumerate(e2n.tolist()):
+        for a, t in enumerate(row):
+            want[t].append((tuple(row), a))
+    seen, row, at = np.zeros(L.N, int), 0, 0
+    for (word_off, n_own, nn, ne, c0, c_run, _, _, _, n_items), it in zip(rec, ids):
+        assert word_off == row and c_run <= n_own <= nn <= 1023 and ne <= 1024
+        nodes = np.concatenate([np.arange(c0, c0 + c_run), it[:n_items]])
+        assert nodes.size == np.unique(nodes).size == nn
+        assert nn == 0 or (nodes.min() >= 0 and nodes.max() < L.N)
+        w = corners[row:row + ne]
+        assert w[:, :, 0].max(initial=0) < max(nn, 1)
+        places = [dict() for _ in range(n_own)]
+        for el in w:
+            for a, (t, place) in enumerate(el):
+                if t < n_own:
+                    assert place not in places[t]
+                    places[t][place] = (tuple(nodes[el[:, 0]].tolist()), a)
+        for t in range(n_own):
+            k = counts[at + t]
+            assert sorted(places[t]) == list(range(k))
+            assert sorted(places[t].values()) == sorted(want[nodes[t]])
+            seen[nodes[t]] += 1
+        row += ne
+        at += n_own
+    assert row == rows and at == counts.size and np.all(seen == 1)
+    L.close()
