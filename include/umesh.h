@@ -123,7 +123,7 @@ typedef enum { UM_BCOL_FIRST_FIT = 0, UM_BCOL_RECOLOUR = 1, UM_BCOL_MIN = 2 } um
  * counter and may be captured in a HIP graph and replayed.  Supported for STAGE_ALL with one or two
  * elements per lane; a plan must not execute concurrently with itself.
  * Plans of the hex loop, and of the edge loop with the LDS-DMA gather or SoA
- * data, need no order between blocks where no cell has more than 8 edges (no
+ * data (binary32: at two elements per lane), need no order between blocks where no cell has more than 8 edges (no
  * node more than 16 elements), no block stages more than 1023 points of a
  * set and the hex loop has at most 2,000,000 elements: they run the owner kernels, in which each point is incremented by
  * one of its blocks only, which evaluates all elements around it, those on

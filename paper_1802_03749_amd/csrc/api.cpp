@@ -660,8 +660,14 @@ um_status um_plan_build(um_ctx ctx, int32_t kernel, const um_arg *args, int32_t 
                          "LDS-DMA gather: HIER plans with the DATAFLOW schedule on AoS data only");
                 build_host_plan(c, p->ea, iter_set, o, p->hp);
                 p->hp.gather = o.gather;
+                // The owner kernel rounds binary32 fluxes as the waiting kernels
+                // do; of those, the SoA one at one edge per lane rounds by
+                // itself (1.2e-7 from the others) and keeps its plans.  The
+                // register gather on AoS data is the waiting kernel by choice:
+                // AoS plans have the LDS-DMA gather for speed.
                 if (p->hp.strategy == UM_STRAT_HIER && p->hp.schedule == UM_SCHED_DATAFLOW &&
-                    (o.gather == UM_GATHER_LDS_DMA || p->ea.layout == UM_SOA))
+                    (p->ea.layout == UM_SOA ? p->ea.dtype == UM_F64 || p->hp.ept == 2
+                                            : o.gather == UM_GATHER_LDS_DMA))
                     build_owner_plan(c, p->ea, o, p->hp);
             } else if (is_step_kernel(kernel)) {
                 if (o.gather != UM_GATHER_REGISTERS)

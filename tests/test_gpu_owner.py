@@ -41,7 +41,7 @@ def random_cells(C, sides, seed):
 def check(mesh, dtype, layout, **kw):
     x, q, adt, e2n, e2c = mesh
     L = EdgeFluxLoop(x, q, adt, e2n, e2c, device=0, layout=layout, dtype=dtype, **kw.pop("loop"))
-    p = L.plan("hier", L.part_block_size or kw.pop("S"), schedule="dataflow",
+    p = L.plan("hier", L.part_block_size or kw.pop("S"), schedule="dataflow", elems_per_thread=2,
                gather="lds_dma" if layout == "aos" else "registers", **kw)
     assert L.export(p, U.UM_EXP_OWNER_RECORDS).size
     sides = L.export(p, U.UM_EXP_OWNER_SIDES)
