@@ -238,6 +238,28 @@ typedef enum { UM_GATHER_REGISTERS = 0, UM_GATHER_LDS_DMA = 1 } um_gather;
  * (same arithmetic in the same order; the sum of squares is reduced the
  * same way).  A time step then reads: edge flux, boundary flux, update +
  * adt, with adt computed once before the first step.  Two launches.
+ *
+ * UM_K_STEP_2D -- the rest of a time step after UM_K_CELL_ADT_2D as one loop
+ * over the cells: edge flux, boundary flux and update, optionally with the
+ * next step's adt.  Args:
+ *   0: q   dim 4 direct, UM_RW
+ *   1: res dim 4 direct, UM_RW
+ *   2: adt dim 1 direct, UM_READ (kept) or UM_RW (then the new state's)
+ *   3: rms dim 1 global, UM_INC
+ *   4: x   via the cell->node map (arity 4), UM_READ
+ *   5: x   via the edge->node map (arity 2), UM_READ
+ *   6: q   via the edge->cell map (arity 2), UM_READ
+ *   7: x   via the boundary-edge->node map (arity 2), UM_READ
+ *   8: q   via the boundary-edge->cell map (arity 1) slot 0, UM_READ
+ * (4 to 7 with idx UM_ALL_SLOTS).  params = {gm1, eps, qinf0..3}.  AoS data;
+ * options as for an edge-flux plan, HIER with the DATAFLOW schedule and the
+ * LDS-DMA gather.  Every side of a cell (from node k to node k + 1 of its
+ * row) must be one edge's or boundary edge's, with the normal pointing out
+ * of the edge's first cell, or nobody's, and every cell needs an edge:
+ * UM_ERR_UNSUPPORTED otherwise.  Results as of the separate loops, to
+ * rounding (the additions to res and rms come in another order); res is
+ * read, and zero afterwards.  Two launches; the plan owns a buffer for the
+ * cells on the borders between its blocks.
  */
 typedef enum {
     UM_K_EDGE_FLUX_LF2D = 0,
@@ -245,7 +267,8 @@ typedef enum {
     UM_K_CELL_ADT_2D = 2,
     UM_K_BOUNDARY_FLUX_2D = 3,
     UM_K_UPDATE_2D = 4,
-    UM_K_UPDATE_ADT_2D = 5
+    UM_K_UPDATE_ADT_2D = 5,
+    UM_K_STEP_2D = 6
 } um_kernel;
 
 /* Map slot value meaning "every slot of the map" (a vector argument). */
@@ -418,7 +441,8 @@ typedef enum {
                                    order of their addition), the
                                    staged positions of the neighbour and of the two
                                    nodes, and the cell's slot in the edge; -1 for a
-                                   missing side.  Hex loop: int32[elements][8][2]
+                                   missing side, neighbour -2 for a boundary edge
+                                   (UM_K_STEP_2D).  Hex loop: int32[elements][8][2]
                                    (records: nodes are owned, "staged nodes" counts
                                    elements): staged position of each corner and, if
                                    that node is owned, the element's place in its sum;

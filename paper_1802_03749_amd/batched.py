@@ -113,11 +113,7 @@ class BatchedSteps:
     def launches_per_step(self) -> int:
         """Kernel launches of one step (what step() enqueues; the adt loop
         only before the first fused step)."""
-        n = 0
-        for ts in self.steps:
-            names = ("flux", "bres", "upa") if ts.fused else ("adt", "flux", "bres", "upd")
-            n += sum(ts.plans[k].stats["n_launches"] for k in names)
-        return n
+        return sum(ts.step_launches() for ts in self.steps)
 
     def zero_rms(self) -> None:
         for ts in self.steps:

@@ -93,6 +93,14 @@ Plan &need(um_plan p) {
     return *p;
 }
 
+void *device_alloc(int64_t n, int64_t &bytes) {
+    void *d = nullptr;
+    if (hipMalloc(&d, size_t(n)) != hipSuccess)
+        fail(UM_ERR_NOMEM, "device allocation of %lld bytes failed", (long long)n);
+    bytes += n;
+    return d;
+}
+
 template <typename T>
 T *upload(const std::vector<T> &v, int64_t &bytes) {
     if (v.empty()) return nullptr;
@@ -105,10 +113,10 @@ T *upload(const std::vector<T> &v, int64_t &bytes) {
 }
 
 void free_device_plan(Plan &p) {
-    void *bufs[17] = {p.dp.emap,  p.dp.binfo, p.dp.stg_c,    p.dp.stg_n, p.dp.loc,
+    void *bufs[20] = {p.dp.emap,  p.dp.binfo, p.dp.stg_c,    p.dp.stg_n, p.dp.loc,
                       p.dp.crun,  p.dp.nrun,  p.dp.pred_off, p.dp.preds, p.dp.frec,
                       p.dp.flags, p.dp.err,   p.dp.partials, p.dp.own_rec, p.dp.own_ids,
-                      p.dp.own_words, p.dp.own_counts};
+                      p.dp.own_words, p.dp.own_counts, p.dp.new_q, p.dp.new_adt, p.dp.shared};
     for (void *b : bufs)
         if (b) hipFree(b);
     p.dp = DevicePlan{};
@@ -285,14 +293,14 @@ LaunchArgs launch_args_hex(Plan &p, const double *params, int32_t nparams, void 
 
 bool is_step_kernel(int32_t k) {
     return k == UM_K_CELL_ADT_2D || k == UM_K_BOUNDARY_FLUX_2D || k == UM_K_UPDATE_2D ||
-           k == UM_K_UPDATE_ADT_2D;
+           k == UM_K_UPDATE_ADT_2D || k == UM_K_STEP_2D;
 }
 
 LaunchArgs launch_args_step(Plan &p, const double *params, int32_t nparams, void *stream) {
     const Ctx &ctx = *p.ctx;
     if (ctx.device < 0) fail(UM_ERR_STATE, "host-only context cannot execute");
     const int want = (p.kernel == UM_K_CELL_ADT_2D || p.kernel == UM_K_UPDATE_ADT_2D) ? 1
-                     : p.kernel == UM_K_BOUNDARY_FLUX_2D                              ? 6
+                     : p.kernel == UM_K_BOUNDARY_FLUX_2D || p.kernel == UM_K_STEP_2D ? 6
                                                                                       : 0;
     if (nparams != want || (want && !params))
         fail(UM_ERR_ARG, "kernel %d takes %d params, got %d", p.kernel, want, nparams);
@@ -318,6 +326,16 @@ LaunchArgs launch_args_step(Plan &p, const double *params, int32_t nparams, void
     if (sa.dat_rms >= 0) la.gbl = static_cast<double *>(ctx.dats[sa.dat_rms].ptr);
     la.partials = p.dp.partials;
     la.n_partials = p.hp.n_partials;
+    la.shared = p.dp.shared;
+    la.n_shared = int32_t(p.hp.owner.shared.size());
+    la.new_q = p.dp.new_q;
+    la.new_adt = p.dp.new_adt;
+    la.keeps_adt = !sa.new_adt;
+    la.own_rec = p.dp.own_rec;
+    la.own_ids = p.dp.own_ids;
+    la.own_words = p.dp.own_words;
+    la.own_stride = p.hp.owner.id_stride;
+    la.own_threads = p.hp.owner.threads;
     if (want >= 1) la.gm1 = params[0];
     if (want == 6) {
         la.eps = params[1];
@@ -670,7 +688,7 @@ um_status um_plan_build(um_ctx ctx, int32_t kernel, const um_arg *args, int32_t 
                                             : o.gather == UM_GATHER_LDS_DMA))
                     build_owner_plan(c, p->ea, o, p->hp);
             } else if (is_step_kernel(kernel)) {
-                if (o.gather != UM_GATHER_REGISTERS)
+                if (o.gather != UM_GATHER_REGISTERS && kernel != UM_K_STEP_2D)
                     fail(UM_ERR_UNSUPPORTED, "LDS-DMA gather: edge flux loop only");
                 p->sa = check_step_args(c, kernel, args, nargs, iter_set);
                 build_host_plan_step(c, kernel, p->sa, iter_set, o, p->hp);
@@ -712,6 +730,13 @@ um_status um_plan_build(um_ctx ctx, int32_t kernel, const um_arg *args, int32_t 
                     std::vector<double> zeros(p->hp.n_partials, 0.0);
                     p->dp.partials = upload(zeros, bytes);
                 }
+                p->dp.shared = upload(p->hp.owner.shared, bytes);
+                if (p->dp.shared) {
+                    const int64_t w = p->sa.dtype == UM_F64 ? 8 : 4;
+                    const int64_t n = int64_t(p->hp.owner.shared.size());
+                    p->dp.new_q = device_alloc(4 * w * n, bytes);
+                    if (p->sa.new_adt) p->dp.new_adt = device_alloc(w * n, bytes);
+                }
                 p->dp.bytes = bytes;
                 UM_HIP(hipDeviceSynchronize());
             }
@@ -745,7 +770,8 @@ um_status um_plan_stats_get(um_plan plan, um_plan_stats *out) {
                 out->n_global_colours = int32_t(hp.colour_off.size()) - 1;
                 out->n_launches = out->n_global_colours;
             } else {
-                const bool two = p.kernel == UM_K_UPDATE_2D || p.kernel == UM_K_UPDATE_ADT_2D;
+                const bool two = p.kernel == UM_K_UPDATE_2D || p.kernel == UM_K_UPDATE_ADT_2D ||
+                                 p.kernel == UM_K_STEP_2D;
                 out->n_launches = hp.n_elem > 0 ? (two ? 2 : 1) : 0;
             }
         } else if (hp.strategy == UM_STRAT_HIER) {
@@ -780,7 +806,9 @@ um_status um_plan_export(um_plan plan, int32_t field, int32_t *host_out, int64_t
         std::vector<int32_t> tmp;
         const std::vector<int32_t> *v = &tmp;
         const bool hier = hp.strategy == UM_STRAT_HIER && !is_step_kernel(p.kernel);
-        if (is_step_kernel(p.kernel) &&
+        const bool owner_field = field == UM_EXP_OWNER_RECORDS || field == UM_EXP_OWNER_IDS ||
+                                 field == UM_EXP_OWNER_SIDES;
+        if (is_step_kernel(p.kernel) && !(p.kernel == UM_K_STEP_2D && owner_field) &&
             !(p.kernel == UM_K_BOUNDARY_FLUX_2D && hp.strategy == UM_STRAT_GLOBAL_COLOUR &&
               (field == UM_EXP_SLOT_ELEMENTS || field == UM_EXP_GLOBAL_COLOURS)))
             fail(UM_ERR_STATE, "field %d is not defined for kernel %d", field, p.kernel);
@@ -908,7 +936,8 @@ um_status um_plan_export(um_plan plan, int32_t field, int32_t *host_out, int64_t
                         const uint32_t slot[4] = {(w0 >> 30) & 1u, w0 >> 31, (w1 >> 30) & 1u,
                                                   w1 >> 31};
                         for (int k = 0; k < 4; ++k)
-                            side(h[k], c[k], c[(k + 1) & 3], slot[k], h[k] != NO_CELL);
+                            side(h[k] == uint32_t(r.nc) ? uint32_t(-2) : h[k], c[k],
+                                 c[(k + 1) & 3], slot[k], h[k] != NO_CELL);
                     } else {
                         const int32_t n = 4 * hp.owner.quads;
                         for (int32_t k = 0; k < n; ++k) {
@@ -962,6 +991,9 @@ void exec_plan(Plan &p, const double *params, int32_t nparams, void *stream, boo
         const bool flow = hp.strategy == UM_STRAT_HIER && hp.schedule == UM_SCHED_DATAFLOW &&
                           !is_step_kernel(p.kernel);
         int32_t *static_ctl = nullptr;
+        if (use_static && p.kernel == UM_K_STEP_2D)
+            fail(UM_ERR_UNSUPPORTED, "static scratch: the step kernel keeps the next state in the "
+                 "plan's own buffers");
         if (use_static) {
             char *base = static_cast<char *>(scratch_address(p.ctx->device));
             if (flow) {
@@ -1030,7 +1062,9 @@ void exec_plan(Plan &p, const double *params, int32_t nparams, void *stream, boo
                     e1 = static_cast<hipEvent_t>(p.events[2 * p.pending_pairs + 1]);
                     UM_HIP(hipEventRecord(e0, la.stream));
                 }
-                const hipError_t le = step_launch_one(la, p.kernel, which, b, e);
+                const hipError_t le = p.kernel == UM_K_STEP_2D
+                                          ? step2d_launch_one(la, which, b, e, hp.owner.lds)
+                                          : step_launch_one(la, p.kernel, which, b, e);
                 if (le != hipSuccess)
                     fail(UM_ERR_HIP, "launch %d of kernel %d (range [%d, %d), %d lanes per "
                          "workgroup, dtype %d) failed: %s", which, p.kernel, b, e, la.block_size,
@@ -1043,6 +1077,9 @@ void exec_plan(Plan &p, const double *params, int32_t nparams, void *stream, boo
             const int32_t n = int32_t(hp.n_elem);
             if (p.kernel == UM_K_CELL_ADT_2D) {
                 step(LAUNCH_DIRECT, 0, n);
+            } else if (p.kernel == UM_K_STEP_2D) {
+                step(LAUNCH_OWNER, 0, int32_t(hp.owner.rec.size()));
+                step(LAUNCH_REDUCE, 0, 1);
             } else if (p.kernel == UM_K_UPDATE_2D || p.kernel == UM_K_UPDATE_ADT_2D) {
                 step(LAUNCH_DIRECT, 0, n);
                 step(LAUNCH_REDUCE, 0, 1);

@@ -59,9 +59,9 @@ __device__ __forceinline__ void lf2d_flux_nocontract(Real xa0, Real xa1, Real xb
     UM_LF2D_FLUX_BODY
 }
 
-// Velocity, pressure and energy plus pressure of a state.  The roundings here
-// and in lf2d_flux_out are written out: they are those that lf2d_flux gets
-// from the compiler's contractions.
+// Velocity, pressure and (binary32) energy plus pressure of a state.  The
+// roundings here and in lf2d_flux_out are written out: in binary32 they are
+// those that lf2d_flux gets from the compiler's contractions.
 template <typename Real>
 struct Flow {
     Real u, v, p, h;
@@ -100,7 +100,7 @@ __device__ __forceinline__ void lf2d_flux_out(Real xa0, Real xa1, Real xb0, Real
     Real F[4];
     if constexpr (sizeof(Real) == 8) {
         F[0] = q[0] * U + r[0] * V;
-        F[3] = s.h * U + t.h * V;
+        F[3] = (q[3] + s.p) * U + (r[3] + t.p) * V;
     } else {
         // binary32: bit for bit lf2d_flux, which rounds cell 1's product only
         F[0] = second ? fma(r[0], V, q[0] * U) : fma(q[0], U, r[0] * V);
@@ -163,6 +163,57 @@ __device__ __forceinline__ void load2(const Real *__restrict__ a, int64_t n, int
     } else {
         v0 = a[g]; v1 = a[n + g];
     }
+}
+
+// Sum over the 64 lanes of a wave in a fixed butterfly; every lane ends
+// with the same value.
+__device__ __forceinline__ double wave_sum(double v) {
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+    return v;
+}
+
+// Fixed-order sum over the workgroup (waves in order); valid in lane 0 of
+// wave 0.  blockDim.x is a multiple of 64, at most 1024.
+__device__ __forceinline__ double block_sum(double v) {
+    __shared__ double wsum[16];
+    v = wave_sum(v);
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    if (lane == 0) wsum[wave] = v;
+    __syncthreads();
+    double t = 0.0;
+    if (threadIdx.x == 0)
+        for (int w = 0; w < int(blockDim.x >> 6); ++w) t += wsum[w];
+    return t;
+}
+
+// The time-step scalar of a cell side by side, its sides in order: velocity and
+// sound speed of its state, then what one side adds, with the contractions
+// that the compiler gives cell_adt written out.
+template <typename Real>
+struct Wave {
+    Real u, v, c;
+};
+
+template <typename Real>
+__device__ __forceinline__ Wave<Real> wave_of(const Real q[4], Real gm1) {
+#pragma clang fp contract(off)
+    const Real ri = Real(1) / q[0];
+    Wave<Real> s;
+    s.u = q[1] * ri;
+    s.v = q[2] * ri;
+    const Real p = gm1 * fma(Real(-0.5), fma(q[1], s.u, q[2] * s.v), q[3]);
+    s.c = sqrt((Real(1) + gm1) * p * ri);
+    return s;
+}
+
+template <typename Real>
+__device__ __forceinline__ Real adt_side(Real xa0, Real xa1, Real xb0, Real xb1,
+                                         const Wave<Real> &s) {
+#pragma clang fp contract(off)
+    const Real mx = xb1 - xa1;
+    const Real my = xa0 - xb0;
+    return fma(s.c, sqrt(fma(my, my, mx * mx)), fabs(fma(s.v, my, s.u * mx)));
 }
 
 }  // namespace dev

@@ -107,6 +107,8 @@ struct StepArgs {
     int32_t dat_x = -1, dat_q = -1, dat_adt = -1, dat_res = -1, dat_rms = -1;
     int32_t layout = UM_AOS;
     int32_t dtype = UM_F64;                      // of x, q and adt
+    int32_t map_c2n = -1, map_e2n = -1, map_e2c = -1;  // UM_K_STEP_2D; boundary maps as above
+    bool new_adt = false;                        // UM_K_STEP_2D: adt is rewritten
 };
 
 // Per-block layout of a hierarchical plan, in launch order.
@@ -161,7 +163,7 @@ struct OwnRec {
     int32_t n_own, nc, nn;     // owned cells, staged cells, staged nodes
     int32_t c_start, c_run, n_start, n_run;
     int32_t node_item, n_items;
-    int32_t own_off;           // hex: owned nodes of the earlier blocks
+    int32_t own_off;           // hex: owned nodes, step: shared cells of the earlier blocks
     int32_t pad;
 };
 static_assert(sizeof(OwnRec) == 48, "OwnRec is 12 words");
@@ -173,7 +175,9 @@ static_assert(sizeof(OwnRec) == 48, "OwnRec is 12 words");
 // cell is that edge's second one:
 //   h0 | h1 << 10 | h2 << 20 | slot0 << 30 | slot1 << 31,
 //   h3 | c0 << 10 | c1 << 20 | slot2 << 30 | slot3 << 31,  c2 | c3 << 10
-// in three planes per block.  General form: 4 * quads words per cell, each
+// in three planes per block.  In the step's plan a boundary side's neighbour
+// is the position after the last staged cell, and c3's word goes on with the
+// cell's number, from 1, among the block's cells that other blocks stage too.  General form: 4 * quads words per cell, each
 // h | a << 10 | b << 20 | slot << 30, NO_SIDE for a missing side.
 // Hex loop: nodes are owned, nc counts the staged nodes and nn the evaluated
 // elements, word_off those of the earlier blocks.  An element's four words:
@@ -183,7 +187,7 @@ static_assert(sizeof(OwnRec) == 48, "OwnRec is 12 words");
 // owned node's sum has.
 constexpr int32_t MAX_NODE_ELEMENTS = 16;
 constexpr uint32_t NO_SIDE = 0xFFFFFFFFu, NO_CELL = 0x3FFu;
-constexpr int32_t MAX_OWNER_POINTS = 1023;     // staged cells, and staged nodes
+constexpr int32_t MAX_OWNER_POINTS = 1022;     // staged cells, and staged nodes
 constexpr int32_t MAX_SIDE_QUADS = 2;          // at most 8 sides per cell
 
 struct OwnerPlan {
@@ -195,6 +199,7 @@ struct OwnerPlan {
     std::vector<int32_t> ids;                  // [n_blocks][id_stride]
     std::vector<uint32_t> words;               // side words, blocks in launch order
     std::vector<uint8_t> counts;               // hex: elements per owned node
+    std::vector<int32_t> shared;               // step: the cells that other blocks stage
 };
 
 struct HostPlan {
@@ -234,8 +239,12 @@ struct HostPlan {
 
 void build_host_plan(const Ctx &ctx, const EdgeArgs &ea, int32_t iter_set,
                      const um_plan_opts &o, HostPlan &hp);
-// Fills hp.owner of a dataflow edge plan where its blocks allow it.
-void build_owner_plan(const Ctx &ctx, const EdgeArgs &ea, const um_plan_opts &o, HostPlan &hp);
+std::vector<int32_t> block_ranges(const Set &is, int32_t block_size, bool &own);
+// Fills hp.owner of a dataflow edge plan where its blocks allow it.  With
+// `sa`, of the whole step's: every cell must then be owned, and its sides are
+// those of its cell->node row, each an edge's or a boundary edge's.
+void build_owner_plan(const Ctx &ctx, const EdgeArgs &ea, const um_plan_opts &o, HostPlan &hp,
+                      const StepArgs *sa = nullptr);
 void build_owner_plan_hex(const Ctx &ctx, const HexArgs &ha, const um_plan_opts &o, HostPlan &hp);
 void build_host_plan_hex(const Ctx &ctx, const HexArgs &ha, int32_t iter_set,
                          const um_plan_opts &o, HostPlan &hp);
@@ -276,6 +285,8 @@ struct DevicePlan {
     uint32_t *own_words = nullptr;
     uint8_t *own_counts = nullptr;
     double *partials = nullptr;                     // UPDATE: one sum per workgroup
+    int32_t *shared = nullptr;                      // STEP: cells that several blocks stage,
+    void *new_q = nullptr, *new_adt = nullptr;      //  their next state, until it is stored
     int64_t bytes = 0;
 };
 

@@ -965,13 +965,26 @@ __device__ __forceinline__ void store4_once(double *__restrict__ a, int64_t n, i
 // 2400x1200 80.9 -> 72.4 (5.8 TB/s of counted traffic), binary32 1133x711 29.5
 // -> 15.9, SoA (staged through registers) 907x613 28.7 -> 15.1.  Blocks that
 // are chunks of the RCM order stage 1.5 times the cells: 33.5 -> 28.6.
-template <int LAYOUT, bool RING, typename Real>
-__global__ __launch_bounds__(1024) void owner_kernel(const OwnRec *__restrict__ recs,
-                                                     const int32_t *__restrict__ ids,
-                                                     int32_t id_stride,
-                                                     const uint32_t *__restrict__ words,
-                                                     int32_t quads, Dats<Real> d, double gm1d,
-                                                     double epsd) {
+// With STEP the residual goes on (step_kernel below): boundary sides have the
+// far field, staged behind the cells, for a neighbour, with the cell's own
+// time-step scalar; then the cell is updated and, with STEP_NEW_ADT, its next
+// time-step scalar evaluated.
+enum { FLUX_ONLY = 0, STEP_KEEP_ADT = 1, STEP_NEW_ADT = 2 };
+
+template <typename Real>
+struct StepOut {
+    Real *q, *adt;          // the state, updated in place where no other block reads it
+    Real *new_q, *new_adt;  // the shared cells' next state
+    double *partials;
+    double qinf[4];
+};
+
+template <int LAYOUT, bool RING, int STEP, typename Real>
+__device__ __forceinline__ void owner_block(const OwnRec *__restrict__ recs,
+                                            const int32_t *__restrict__ ids, int32_t id_stride,
+                                            const uint32_t *__restrict__ words, int32_t quads,
+                                            const Dats<Real> &d, double gm1d, double epsd,
+                                            const StepOut<Real> &out) {
     constexpr bool F64 = sizeof(Real) == 8;
     constexpr bool DMA = LAYOUT == UM_AOS;
     extern __shared__ double lds[];
@@ -987,11 +1000,13 @@ __global__ __launch_bounds__(1024) void owner_kernel(const OwnRec *__restrict__ 
     const int n_items = rec.n_items;
     const int32_t c_start = rec.c_start, n_start = rec.n_start;
 
-    Real *q_a = reinterpret_cast<Real *>(lds);  // F64: [nc] x (q0, q1); F32: [nc] x q[4]
-    Real *q_b = q_a + 2 * nc;                   // F64: [nc] x (q2, q3)
-    Real *x_a = q_a + 4 * nc;                   // F64: [nn] x (x, y); F32: [nn] x
+    // staged cells; the step's far field is one more
+    const int ns = STEP == FLUX_ONLY ? nc : nc + 1;
+    Real *q_a = reinterpret_cast<Real *>(lds);  // F64: [ns] x (q0, q1); F32: [ns] x q[4]
+    Real *q_b = q_a + 2 * ns;                   // F64: [ns] x (q2, q3)
+    Real *x_a = q_a + 4 * ns;                   // F64: [nn] x (x, y); F32: [nn] x
     Real *x_b = x_a + nn;                       // F32: [nn] y
-    uint32_t *adt_w = reinterpret_cast<uint32_t *>(x_a + 2 * nn);  // F64: [2][nc] words
+    uint32_t *adt_w = reinterpret_cast<uint32_t *>(x_a + 2 * nn);  // F64: [2][ns] words
     const __amdgpu_buffer_rsrc_t rq = rsrc_of(d.q, 4 * sizeof(Real) * d.C);
     const __amdgpu_buffer_rsrc_t ra = rsrc_of(d.adt, sizeof(Real) * d.C);
     const __amdgpu_buffer_rsrc_t rx = rsrc_of(d.x, 2 * sizeof(Real) * d.N);
@@ -1018,7 +1033,7 @@ __global__ __launch_bounds__(1024) void owner_kernel(const OwnRec *__restrict__ 
             dma<16>(rq, q_a + 2 * t0, 32 * g);
             dma<16>(rq, q_b + 2 * t0, 32 * g + 16);
             dma<4>(ra, adt_w + t0, 8 * g);
-            dma<4>(ra, adt_w + nc + t0, 8 * g + 4);
+            dma<4>(ra, adt_w + ns + t0, 8 * g + 4);
         } else if constexpr (DMA) {
             dma<16>(rq, q_a + 4 * t0, 16 * g);
             dma<4>(ra, adt_w + t0, 4 * g);
@@ -1032,7 +1047,7 @@ __global__ __launch_bounds__(1024) void owner_kernel(const OwnRec *__restrict__ 
                 *reinterpret_cast<f64x2 *>(q_b + 2 * t) = f64x2{v[2], v[3]};
                 const uint64_t b = __builtin_bit_cast(uint64_t, a);
                 adt_w[t] = uint32_t(b);
-                adt_w[nc + t] = uint32_t(b >> 32);
+                adt_w[ns + t] = uint32_t(b >> 32);
             } else {
                 *reinterpret_cast<float4 *>(q_a + 4 * t) = make_float4(v[0], v[1], v[2], v[3]);
                 adt_w[t] = __builtin_bit_cast(uint32_t, a);
@@ -1073,6 +1088,13 @@ __global__ __launch_bounds__(1024) void owner_kernel(const OwnRec *__restrict__ 
             if (t0 + lane < nn) node_in(t0, g);
         }
     }
+    if constexpr (STEP != FLUX_ONLY) {
+        if (tid < 4) {
+            const double v = tid == 0 ? out.qinf[0] : tid == 1 ? out.qinf[1]
+                             : tid == 2 ? out.qinf[2] : out.qinf[3];
+            (F64 && tid >= 2 ? q_b + 2 * nc - 2 : q_a + (F64 ? 2 : 4) * nc)[tid] = Real(v);
+        }
+    }
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
 
@@ -1081,7 +1103,7 @@ __global__ __launch_bounds__(1024) void owner_kernel(const OwnRec *__restrict__ 
             const f64x2 lo = *reinterpret_cast<const f64x2 *>(q_a + 2 * t);
             const f64x2 hi = *reinterpret_cast<const f64x2 *>(q_b + 2 * t);
             q[0] = lo.x; q[1] = lo.y; q[2] = hi.x; q[3] = hi.y;
-            a = __builtin_bit_cast(double, uint64_t(adt_w[t]) | (uint64_t(adt_w[nc + t]) << 32));
+            a = __builtin_bit_cast(double, uint64_t(adt_w[t]) | (uint64_t(adt_w[ns + t]) << 32));
         } else {
             const float4 v = *reinterpret_cast<const float4 *>(q_a + 4 * t);
             q[0] = v.x; q[1] = v.y; q[2] = v.z; q[3] = v.w;
@@ -1096,6 +1118,7 @@ __global__ __launch_bounds__(1024) void owner_kernel(const OwnRec *__restrict__ 
             x0 = x_a[t]; x1 = x_b[t];
         }
     };
+    double squares = 0.0;
     if (tid < n_own) {
         Real q[4], a;
         state(tid, q, a);
@@ -1104,34 +1127,43 @@ __global__ __launch_bounds__(1024) void owner_kernel(const OwnRec *__restrict__ 
         auto side = [&](int h, Real xa0, Real xa1, Real xb0, Real xb1, bool second) {
             Real qh[4], ah, f[4];
             state(h, qh, ah);
+            if (STEP != FLUX_ONLY && h == nc) ah = a;
             dev::lf2d_flux_out<LAYOUT == UM_SOA>(xa0, xa1, xb0, xb1, q, own, qh,
                                                  dev::flow_of(qh, gm1), a, ah, eps, second, f);
 #pragma unroll
             for (int c = 0; c < 4; ++c) r[c] += double(f[c]);
         };
+        // a residual that held something is zero after the step
+        bool held = false;
+        if constexpr (STEP != FLUX_ONLY) {
+#pragma unroll
+            for (int c = 0; c < 4; ++c) held = held || __builtin_bit_cast(uint64_t, r[c]) != 0;
+        }
         // one side at a time: unrolled, the loads of all sides are issued first
         // and their registers leave room for fewer wavefronts
-        if constexpr (RING) {
-            Real xa0, xa1, xb0, xb1, xc0, xc1;
-            node(int((w.y >> 10) & 0x3FFu), xa0, xa1);
-            xc0 = xa0; xc1 = xa1;
-            uint32_t hs = w.x, next = (w.y >> 20) & 0x3FFu, rest = w.z;
+        // (the first corner is read again at the end of the ring: two registers
+        // pairs less, 64 in all, room for an eighth wavefront)
+        auto walk = [&](auto &&visit) {
+            const uint32_t c0 = (w.y >> 10) & 0x3FFu;
+            uint32_t hs = w.x, next = (w.y >> 20) & 0x3FFu, rest = (w.z & 0xFFFFFu) | c0 << 20;
             uint32_t slots = (w.x >> 30) | ((w.y >> 30) << 2);
+            Real xa0, xa1, xb0, xb1;
+            node(int(c0), xa0, xa1);
 #pragma unroll 1
             for (int k = 0; k < 4; ++k) {
-                if (k < 3) {
-                    node(int(next), xb0, xb1);
-                } else {
-                    xb0 = xc0; xb1 = xc1;
-                }
-                const uint32_t h = hs & 0x3FFu;
-                if (h != NO_CELL) side(int(h), xa0, xa1, xb0, xb1, slots & 1u);
+                node(int(next), xb0, xb1);
+                visit(hs & 0x3FFu, xa0, xa1, xb0, xb1, slots & 1u);
                 xa0 = xb0; xa1 = xb1;
                 next = rest & 0x3FFu;
                 rest >>= 10;
                 hs = k == 2 ? w.y : hs >> 10;
                 slots >>= 1;
             }
+        };
+        if constexpr (RING) {
+            walk([&](uint32_t h, Real xa0, Real xa1, Real xb0, Real xb1, bool second) {
+                if (h != NO_CELL) side(int(h), xa0, xa1, xb0, xb1, second);
+            });
         } else {
 #pragma unroll 1
             for (int k = 0; k < 4 * quads; ++k) {
@@ -1145,8 +1177,100 @@ __global__ __launch_bounds__(1024) void owner_kernel(const OwnRec *__restrict__ 
                 side(int(s & 0x3FFu), xa0, xa1, xb0, xb1, (s >> 30) & 1u);
             }
         }
-        store4_once<LAYOUT>(d.res, d.C, own_id, r);
+        if constexpr (STEP == FLUX_ONLY) {
+            store4_once<LAYOUT>(d.res, d.C, own_id, r);
+        } else {
+            Real qn[4];
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                const double change = r[c] / double(a);
+                qn[c] = Real(double(q[c]) - change);
+                squares = fma(change, change, squares);
+                r[c] = 0.0;
+                // one division at a time: four in flight take 20 more registers
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            if (held) store4<LAYOUT>(d.res, d.C, own_id, r);
+            const uint32_t number = w.z >> 20;
+            const int64_t to = number ? rec.own_off + int64_t(number) - 1 : own_id;
+            Real *const new_q = number ? out.new_q : out.q;
+            if constexpr (F64) {
+                f64x2 *p = reinterpret_cast<f64x2 *>(new_q + 4 * to);
+                p[0] = f64x2{qn[0], qn[1]};
+                p[1] = f64x2{qn[2], qn[3]};
+            } else {
+                reinterpret_cast<float4 *>(new_q)[to] = make_float4(qn[0], qn[1], qn[2], qn[3]);
+            }
+            if constexpr (STEP == STEP_NEW_ADT) {
+                const dev::Wave<Real> wave = dev::wave_of(qn, gm1);
+                Real sum = Real(0);
+                walk([&](uint32_t, Real xa0, Real xa1, Real xb0, Real xb1, bool) {
+                    sum = sum + dev::adt_side(xa0, xa1, xb0, xb1, wave);
+                });
+                (number ? out.new_adt : out.adt)[to] = sum;
+            }
+        }
     }
+    if constexpr (STEP != FLUX_ONLY) {
+        const double t = dev::block_sum(squares);
+        if (tid == 0) out.partials[pos] = t;
+    }
+}
+
+template <int LAYOUT, bool RING, typename Real>
+__global__ __launch_bounds__(1024) void owner_kernel(const OwnRec *__restrict__ recs,
+                                                     const int32_t *__restrict__ ids,
+                                                     int32_t id_stride,
+                                                     const uint32_t *__restrict__ words,
+                                                     int32_t quads, Dats<Real> d, double gm1,
+                                                     double eps) {
+    owner_block<LAYOUT, RING, FLUX_ONLY, Real>(recs, ids, id_stride, words, quads, d, gm1, eps, {});
+}
+
+// A time step's edge flux, boundary flux and update (with NEW_ADT also the
+// next step's time-step scalar) in one pass over the cells, in place where a
+// cell's only reader is its own block, which has it staged.  Cells on the
+// borders between blocks (a quarter, at 16x16 cells) go to a buffer of the
+// plan, and finish_kernel stores them.  A step of 1200x600 cells, binary64 (the
+// separate loops, with the flux by owner_kernel -> here): 51.2 -> 37.6 us, 7
+// launches -> 2; 353x241 cells, binary32, adt by its own loop: 26.5 -> 13.1.
+// The kernel takes 32 us for 108 MB of counted traffic, 13 more than
+// owner_kernel: the update's divisions and the square roots of adt double the
+// arithmetic (8.7 instead of 4.6 million vector instructions).  Writing every
+// cell's next state to a buffer and copying it back took 41.6 us in all.
+template <int STEP, typename Real>
+__global__ __launch_bounds__(1024) void step_kernel(const OwnRec *__restrict__ recs,
+                                                    const int32_t *__restrict__ ids,
+                                                    int32_t id_stride,
+                                                    const uint32_t *__restrict__ words,
+                                                    Dats<Real> d, double gm1, double eps,
+                                                    StepOut<Real> out) {
+    owner_block<UM_AOS, true, STEP, Real>(recs, ids, id_stride, words, 1, d, gm1, eps, out);
+}
+
+// Workgroup 0 adds the partial sums in a fixed order to the global target;
+// the others store the shared cells' next state, 16 bytes per lane and pass.
+template <typename Real>
+__global__ __launch_bounds__(256) void finish_kernel(const int32_t *__restrict__ shared,
+                                                     int32_t n_shared,
+                                                     const Real *__restrict__ new_q,
+                                                     const Real *__restrict__ new_adt,
+                                                     Real *__restrict__ q, Real *__restrict__ adt,
+                                                     const double *__restrict__ partials,
+                                                     int32_t n_partials, double *__restrict__ gbl) {
+    if (blockIdx.x == 0) {
+        double acc = 0.0;
+        for (int32_t i = threadIdx.x; i < n_partials; i += 256) acc += partials[i];
+        const double t = dev::block_sum(acc);
+        if (threadIdx.x == 0) gbl[0] += t;
+        return;
+    }
+    constexpr int P = sizeof(Real) / 4;  // pieces per cell
+    const int64_t i = int64_t(blockIdx.x - 1) * 256 + threadIdx.x;
+    if (i >= int64_t(P) * n_shared) return;
+    const int64_t c = shared[i / P];
+    reinterpret_cast<u32x4 *>(q)[c * P + i % P] = reinterpret_cast<const u32x4 *>(new_q)[i];
+    if (new_adt && i % P == 0) adt[c] = new_adt[i / P];
 }
 
 template <int LAYOUT, typename Real>
@@ -1354,6 +1478,45 @@ hipError_t lf2d_launch_one(const LaunchArgs &la, int which, int32_t begin, int32
                    : launch_typed<UM_AOS, float>(la, which, begin, end, lds);
     return f64 ? launch_typed<UM_SOA, double>(la, which, begin, end, lds)
                : launch_typed<UM_SOA, float>(la, which, begin, end, lds);
+}
+
+namespace {
+
+template <typename Real>
+hipError_t step2d_typed(const LaunchArgs &la, int which, int32_t begin, int32_t end, int64_t lds) {
+    Real *q = const_cast<Real *>(static_cast<const Real *>(la.q));
+    Real *adt = const_cast<Real *>(static_cast<const Real *>(la.adt));
+    if (end - begin <= 0) return hipSuccess;
+    clear_stale_error();
+    if (which == LAUNCH_OWNER) {
+        const Dats<Real> d{static_cast<const Real *>(la.x), q, adt, la.res, la.N, la.C};
+        const StepOut<Real> out{q, adt, static_cast<Real *>(la.new_q),
+                                static_cast<Real *>(la.new_adt), la.partials,
+                                {la.qinf[0], la.qinf[1], la.qinf[2], la.qinf[3]}};
+        auto kern = la.keeps_adt ? step_kernel<STEP_KEEP_ADT, Real> : step_kernel<STEP_NEW_ADT, Real>;
+        const hipError_t ea = allow_lds(reinterpret_cast<const void *>(kern), lds);
+        if (ea != hipSuccess) return ea;
+        hipLaunchKernelGGL(kern, dim3(end - begin), dim3(la.own_threads), size_t(lds), la.stream,
+                           la.own_rec, la.own_ids, la.own_stride, la.own_words, d, la.gm1, la.eps,
+                           out);
+    } else if (which == LAUNCH_REDUCE) {
+        const int64_t pieces = int64_t(la.n_shared) * int64_t(sizeof(Real)) / 4;
+        hipLaunchKernelGGL((finish_kernel<Real>), dim3(unsigned(1 + (pieces + 255) / 256)), dim3(256),
+                           0, la.stream, la.shared, la.n_shared,
+                           static_cast<const Real *>(la.new_q), static_cast<const Real *>(la.new_adt),
+                           q, adt, la.partials, la.n_partials, la.gbl);
+    } else {
+        return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t step2d_launch_one(const LaunchArgs &la, int which, int32_t begin, int32_t end,
+                             int64_t lds) {
+    return la.dtype == UM_F32 ? step2d_typed<float>(la, which, begin, end, lds)
+                              : step2d_typed<double>(la, which, begin, end, lds);
 }
 
 }  // namespace um

@@ -24,6 +24,7 @@
 namespace um {
 namespace {
 
+using dev::block_sum;
 using dev::lf2d_flux;
 using dev::load2;
 using dev::load4;
@@ -119,28 +120,6 @@ __global__ __launch_bounds__(1024) void bres_kernel(const Real *__restrict__ x,
         for (int k = 0; k < 4; ++k) r[k] += double(f[k]);
         store4<LAYOUT>(res, C, c, r);
     }
-}
-
-// Sum over the 64 lanes of a wave in a fixed butterfly; every lane ends
-// with the same value.
-__device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-    return v;
-}
-
-// Fixed-order sum over the workgroup (waves in order); valid in lane 0 of
-// wave 0.  blockDim.x is a multiple of 64, at most 1024.
-__device__ __forceinline__ double block_sum(double v) {
-    __shared__ double wsum[16];
-    v = wave_sum(v);
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    if (lane == 0) wsum[wave] = v;
-    __syncthreads();
-    double t = 0.0;
-    if (threadIdx.x == 0)
-        for (int w = 0; w < int(blockDim.x >> 6); ++w) t += wsum[w];
-    return t;
 }
 
 // Update: d = res / adt in double, q rounded once to its storage type.

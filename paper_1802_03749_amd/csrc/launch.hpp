@@ -43,6 +43,10 @@ struct LaunchArgs {
     double qinf[4];        // BOUNDARY_FLUX: far-field state
     double *partials;      // UPDATE: per-workgroup sums
     double *gbl;           // UPDATE: the global reduction target
+    const int32_t *shared; // STEP: cells that several blocks stage,
+    void *new_q, *new_adt; //  their next state, until it is stored
+    int32_t n_shared;
+    int32_t keeps_adt;     // STEP: 1 if adt is not rewritten
     int32_t n_partials;
 };
 
@@ -80,6 +84,12 @@ inline hipError_t allow_lds(const void *kernel, int64_t lds) {
 // colour; ATOMIC and DEBUG cover elements [0, end - begin).
 hipError_t lf2d_launch_one(const LaunchArgs &la, int which, int32_t begin, int32_t end,
                            int64_t lds_bytes);
+
+// The launches of the step kernel: OWNER over blocks [begin, end) writing
+// the next state, the shared cells' to new_q (and new_adt), and one partial
+// sum per block, then REDUCE storing those cells' and adding the sums to gbl.
+hipError_t step2d_launch_one(const LaunchArgs &la, int which, int32_t begin, int32_t end,
+                             int64_t lds_bytes);
 
 // The same for the hex element loop (x in x, v in q, force in res, kappa in
 // gm1; emap holds 8 node ids per slot).

@@ -206,31 +206,38 @@ static bool tabu_colouring(const std::vector<int64_t> &adj_off, const std::vecto
     return true;
 }
 
+// Plan blocks of a set as element ranges: the set's partition if built for
+// this size; groups of k consecutive partition blocks if built for
+// block_size / k (bisection order keeps consecutive blocks adjacent in
+// space); else chunks.  `own` says whether they are the partition's own.
+std::vector<int32_t> block_ranges(const Set &is, int32_t block_size, bool &own) {
+    const int64_t E = is.size;
+    const int32_t pbs = is.part_block_size;
+    std::vector<int32_t> off;
+    own = false;
+    if (pbs > 0 && !is.part_off.empty() && block_size % pbs == 0) {
+        const int32_t k = block_size / pbs;
+        own = k == 1;
+        const int32_t npb = int32_t(is.part_off.size()) - 1;
+        for (int32_t b = 0; b < npb; b += k) off.push_back(is.part_off[b]);
+        off.push_back(is.part_off[npb]);
+    } else {
+        for (int64_t s = 0; s < E; s += block_size) off.push_back(int32_t(s));
+        off.push_back(int32_t(E));
+        if (E == 0) off.assign(1, 0);
+    }
+    return off;
+}
+
 // Blocks, layer-1 colouring, launch order and dataflow predecessors: the
 // part of a hierarchical plan that only depends on which points each
 // element writes (wt: [E][arity] into 0..C-1).  Returns the colour count.
 int32_t plan_blocks(const Ctx &ctx, int32_t iter_set, const int32_t *wt, int arity, int64_t C,
                     const um_plan_opts &o, HostPlan &hp) {
-    const int64_t E = ctx.sets[iter_set].size;
-    // ---- blocks: the set's partition if built for this size; groups of k
-    // consecutive partition blocks if built for block_size / k (bisection
-    // order keeps consecutive blocks adjacent in space); else chunks
+    // ---- blocks
     const Set &is = ctx.sets[iter_set];
-    const int32_t pbs = is.part_block_size;
     bool partition_blocks = false;  // plan blocks are the partition's own blocks
-    if (pbs > 0 && !is.part_off.empty() && o.block_size % pbs == 0) {
-        const int32_t k = o.block_size / pbs;
-        partition_blocks = k == 1;
-        const int32_t npb = int32_t(is.part_off.size()) - 1;
-        hp.blk_off.clear();
-        for (int32_t b = 0; b < npb; b += k) hp.blk_off.push_back(is.part_off[b]);
-        hp.blk_off.push_back(is.part_off[npb]);
-    } else {
-        hp.blk_off.clear();
-        for (int64_t s = 0; s < E; s += o.block_size) hp.blk_off.push_back(int32_t(s));
-        hp.blk_off.push_back(int32_t(E));
-        if (E == 0) hp.blk_off.assign(1, 0);
-    }
+    hp.blk_off = block_ranges(is, o.block_size, partition_blocks);
     const int32_t nb = int32_t(hp.blk_off.size()) - 1;
 
     // ---- layer 1: block colouring.  For every cell, the blocks that write

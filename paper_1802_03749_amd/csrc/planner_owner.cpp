@@ -91,6 +91,7 @@ struct Around {
     std::vector<int32_t> own_off, own;   // per block: its points, ascending
     std::vector<int32_t> inc;            // [points][D]: arity * element + slot, ascending
     std::vector<uint8_t> deg;            // how many of them
+    std::vector<int32_t> owner;          // per point, -1 if no block touches it
 
     // Owner of a point: the first of the blocks that touch it or, where that
     // leaves the blocks' points in fewer runs of consecutive ids, the last.
@@ -123,18 +124,37 @@ struct Around {
         for (int64_t p = 1; p < P; ++p)
             if (first[p] >= 0 && first[p - 1] >= 0)
                 breaks += (last[p] != last[p - 1]) - (first[p] != first[p - 1]);
-        const std::vector<int32_t> &owner = breaks < 0 ? last : first;
         own_off.assign(nb + 1, 0);
+        if (breaks < 0)
+            for (int64_t p = 0; p < P; ++p)
+                if (first[p] >= 0) first[p] = last[p];
+        owner.swap(first);
         for (int64_t p = 0; p < P; ++p)
-            if (first[p] >= 0) own_off[owner[p] + 1]++;
+            if (owner[p] >= 0) own_off[owner[p] + 1]++;
         for (int32_t b = 0; b < nb; ++b) own_off[b + 1] += own_off[b];
         own.resize(own_off[nb]);
         std::vector<int32_t> fill(own_off.begin(), own_off.end() - 1);
         for (int64_t p = 0; p < P; ++p)
-            if (first[p] >= 0) own[fill[owner[p]]++] = int32_t(p);
+            if (owner[p] >= 0) own[fill[owner[p]]++] = int32_t(p);
         return true;
     }
 };
+
+// Per cell, bit k set if a boundary edge (nodes a, b; its cell) is the cell's
+// side from node k to node k + 1; false if one is none of its cell's sides or
+// two are the same.
+bool far_sides(const std::vector<int32_t> &b2c, const std::vector<int32_t> &b2n,
+               const int32_t *c2n, int64_t C, std::vector<uint8_t> &far) {
+    far.assign(C, 0);
+    for (size_t e = 0; e < b2c.size(); ++e) {
+        const int32_t *n = c2n + 4 * int64_t(b2c[e]);
+        int k = 0;
+        while (k < 4 && (n[k] != b2n[2 * e] || n[(k + 1) & 3] != b2n[2 * e + 1])) ++k;
+        if (k == 4 || far[b2c[e]] >> k & 1) return false;
+        far[b2c[e]] |= uint8_t(1 << k);
+    }
+    return true;
+}
 
 uint16_t *zeroed(int64_t n) {
     void *p = std::calloc(size_t(std::max<int64_t>(n, 1)), sizeof(uint16_t));
@@ -213,6 +233,20 @@ bool arrange(const Side *side, int32_t n, Side s[4], uint32_t corner[4]) {
     return true;
 }
 
+// Places the n sides at the corners they run between, and the boundary
+// sides' marks; false if a side is none of those or taken.
+bool place(const Side *side, int32_t n, uint8_t far, uint32_t far_pos, const uint32_t corner[4],
+           Side s[4]) {
+    for (int k = 0; k < 4; ++k) s[k] = Side{far >> k & 1 ? far_pos : NO_CELL, 0, 0, 0};
+    for (int32_t i = 0; i < n; ++i) {
+        int k = 0;
+        while (k < 4 && (corner[k] != side[i].a || corner[(k + 1) & 3] != side[i].b)) ++k;
+        if (k == 4 || s[k].h != NO_CELL) return false;
+        s[k] = side[i];
+    }
+    return true;
+}
+
 // Runs work(b0, b1) over [0, nb) in as many ranges as threads are worth it
 // for E elements, each on its own thread; the largest result.
 template <typename F>
@@ -246,11 +280,12 @@ auto in_ranges(int32_t nb, int64_t E, F work) {
 
 }  // namespace
 
-void build_owner_plan(const Ctx &ctx, const EdgeArgs &ea, const um_plan_opts &o, HostPlan &hp) {
+void build_owner_plan(const Ctx &ctx, const EdgeArgs &ea, const um_plan_opts &o, HostPlan &hp,
+                      const StepArgs *sa) {
     const Map &mc = ctx.maps[ea.map_c];
     const Map &mn = ctx.maps[ea.map_n];
     const int64_t C = ctx.sets[mc.to].size, N = ctx.sets[mn.to].size;
-    const int64_t E = hp.n_elem;
+    const int64_t E = int64_t(mc.table.size()) / 2;
     const int32_t nb = int32_t(hp.blk_off.size()) - 1;
     OwnerPlan &op = hp.owner;
     op = OwnerPlan{};
@@ -259,7 +294,15 @@ void build_owner_plan(const Ctx &ctx, const EdgeArgs &ea, const um_plan_opts &o,
     Around ar;
     if (!ar.build(mc, C, hp.blk_off, {4, 4 * MAX_SIDE_QUADS})) return;
     op.quads = ar.D / 4;
-    const auto &[D, own_off, own, inc, deg] = ar;
+    const auto &[D, own_off, own, inc, deg, owner] = ar;
+    const int32_t *rows_c2n = nullptr;
+    std::vector<uint8_t> far;  // per cell: which sides are boundary edges'
+    if (sa) {
+        if (int64_t(own.size()) != C || op.quads != 1) return;
+        rows_c2n = ctx.maps[sa->map_c2n].table.data();
+        if (!far_sides(ctx.maps[sa->map_c].table, ctx.maps[sa->map_n].table, rows_c2n, C, far))
+            return;
+    }
 
     const int64_t w = ea.dtype == UM_F64 ? 8 : 4;
     const std::vector<int32_t> order =
@@ -274,7 +317,7 @@ void build_owner_plan(const Ctx &ctx, const EdgeArgs &ea, const um_plan_opts &o,
         rows += op.rec[k].n_own;
         op.n_own_max = std::max(op.n_own_max, op.rec[k].n_own);
     }
-    std::vector<std::vector<int32_t>> items(nb);
+    std::vector<std::vector<int32_t>> items(nb), shared(nb);
     enum Result { OK = 0, NO_RING = 1, TOO_LARGE = 2 };
     // the records, listed ids and side words of blocks [b0, b1)
     auto plan_range = [&](int32_t b0, int32_t b1, bool ring) -> Result {
@@ -306,6 +349,14 @@ void build_owner_plan(const Ctx &ctx, const EdgeArgs &ea, const um_plan_opts &o,
                             nodes.push_back(mn.table[t]);
                         }
                 }
+            if (sa)
+                for (int32_t i = 0; i < 4 * r.n_own; ++i) {
+                    const int32_t n = rows_c2n[4 * int64_t(cells[i / 4]) + i % 4];
+                    if (!npos[n]) {
+                        npos[n] = 1;
+                        nodes.push_back(n);
+                    }
+                }
             std::sort(cells.begin() + r.n_own, cells.end());
             std::sort(nodes.begin(), nodes.end());
             r.nc = int32_t(cells.size());
@@ -327,12 +378,24 @@ void build_owner_plan(const Ctx &ctx, const EdgeArgs &ea, const um_plan_opts &o,
                                 npos[mn.table[there]] - 1u, uint32_t(here & 1)};
                 }
                 if (ring) {
-                    if (!arrange(s, n, g, corner)) return NO_RING;
+                    if (sa) {
+                        for (int j = 0; j < 4; ++j)
+                            corner[j] = npos[rows_c2n[4 * int64_t(cells[i]) + j]] - 1u;
+                        if (!place(s, n, far[cells[i]], uint32_t(r.nc), corner, g)) return NO_RING;
+                    } else if (!arrange(s, n, g, corner)) {
+                        return NO_RING;
+                    }
                     uint32_t *w = &op.words[3 * size_t(r.word_off) + i];
                     w[0] = g[0].h | g[1].h << 10 | g[2].h << 20 | g[0].slot << 30 | g[1].slot << 31;
                     w[r.n_own] =
                         g[3].h | corner[0] << 10 | corner[1] << 20 | g[2].slot << 30 | g[3].slot << 31;
                     w[2 * r.n_own] = corner[2] | corner[3] << 10;
+                    if (sa && std::any_of(s, s + n, [&](const Side &t) {
+                            return owner[cells[t.h]] != b;
+                        })) {
+                        shared[k].push_back(cells[i]);
+                        w[2 * r.n_own] |= uint32_t(shared[k].size()) << 20;
+                    }
                 } else {
                     uint32_t *w = &op.words[(size_t(r.word_off) + i) * D];
                     for (int32_t j = 0; j < D; ++j)
@@ -355,7 +418,7 @@ void build_owner_plan(const Ctx &ctx, const EdgeArgs &ea, const um_plan_opts &o,
     };
     Result res = op.quads == 1 ? OK : NO_RING;
     for (bool ring : {true, false}) {
-        if (ring && res != OK) continue;
+        if (ring ? res != OK : sa != nullptr) continue;
         op.ring = ring;
         op.words.assign(size_t(rows) * (ring ? 3 : D), 0u);
         res = in_ranges(nb, E, [&](int32_t b0, int32_t b1) { return plan_range(b0, b1, ring); });
@@ -363,15 +426,18 @@ void build_owner_plan(const Ctx &ctx, const EdgeArgs &ea, const um_plan_opts &o,
     }
     for (const OwnRec &r : op.rec) {
         op.id_stride = std::max(op.id_stride, r.n_items);
-        op.lds = std::max(op.lds, owner_lds_bytes(ea.dtype, r.nc, r.nn));
+        op.lds = std::max(op.lds, owner_lds_bytes(ea.dtype, r.nc + (sa ? 1 : 0), r.nn));
     }
     if (res != OK || op.lds > (o.lds_limit_bytes > 0 ? o.lds_limit_bytes : ctx.lds_limit)) {
         op = OwnerPlan{};
         return;
     }
     op.ids.assign(size_t(nb) * op.id_stride, 0);
-    for (int32_t k = 0; k < nb; ++k)
+    for (int32_t k = 0; k < nb; ++k) {
         std::copy(items[k].begin(), items[k].end(), op.ids.begin() + size_t(k) * op.id_stride);
+        op.rec[k].own_off = int32_t(op.shared.size());
+        op.shared.insert(op.shared.end(), shared[k].begin(), shared[k].end());
+    }
     op.threads = std::max(64, (op.n_own_max + 63) / 64 * 64);  // a lane per owned cell
     op.use = true;
 }
@@ -394,7 +460,7 @@ void build_owner_plan_hex(const Ctx &ctx, const HexArgs &ha, const um_plan_opts 
     if (nb <= 0 || E > 2000000) return;
     Around ar;
     if (!ar.build(m, N, hp.blk_off, {8, MAX_NODE_ELEMENTS})) return;
-    const auto &[D, own_off, own, inc, deg] = ar;
+    const auto &[D, own_off, own, inc, deg, owner] = ar;
     for (uint8_t n : deg) op.quads = std::max<int32_t>(op.quads, n);
 
     const std::vector<int32_t> order = launch_order(nb, o, N * 72 + E * 24);

@@ -139,6 +139,40 @@ StepArgs check_step_args(const Ctx &ctx, int32_t kernel, const um_arg *args, int
         if (sa.dat_q == sa.dat_res) fail(UM_ERR_ARITY, "update + adt kernel: q and res must differ");
         check_layouts(ctx, {sa.dat_x, sa.dat_q, sa.dat_res, sa.dat_adt}, "update + adt");
         sa.dtype = check_real(ctx, {sa.dat_x, sa.dat_q, sa.dat_adt}, "update + adt");
+    } else if (kernel == UM_K_STEP_2D) {
+        const bool keep = nargs == 9 && args && args[2].acc == UM_READ;
+        const Want w[5] = {{4, 0, 0, UM_RW, "q", true},
+                           {4, 0, 0, UM_RW, "res", false},
+                           {1, 0, 0, keep ? UM_READ : UM_RW, "adt", true},
+                           {1, UM_GLOBAL, 0, UM_INC, "rms", false},
+                           {2, 4, UM_ALL_SLOTS, UM_READ, "x", true}};
+        if (nargs != 9 || !args) fail(UM_ERR_ARITY, "step kernel takes 9 args, got %d", nargs);
+        check_pattern(ctx, args, 5, iter, w, 5, "step");
+        sa.dat_q = args[0].dat;
+        sa.dat_res = args[1].dat;
+        sa.dat_adt = args[2].dat;
+        sa.dat_rms = args[3].dat;
+        sa.dat_x = args[4].dat;
+        sa.map_c2n = args[4].map;
+        sa.new_adt = !keep;
+        const int32_t dat[4] = {sa.dat_x, sa.dat_q, sa.dat_x, sa.dat_q}, arity[4] = {2, 2, 2, 1};
+        for (int i = 5; i < 9; ++i) {
+            const um_arg &a = args[i];
+            if (a.map < 0 || a.map >= int32_t(ctx.maps.size()))
+                fail(UM_ERR_ARITY, "arg %d: must be accessed through a map", i);
+            const Map &m = ctx.maps[a.map];
+            if (a.dat != dat[i - 5] || a.idx != (i == 8 ? 0 : UM_ALL_SLOTS) || a.acc != UM_READ ||
+                m.arity != arity[i - 5] || m.to != ctx.dats[a.dat].set ||
+                m.from != ctx.maps[args[i <= 6 ? 5 : 7].map].from)
+                fail(UM_ERR_ARITY, "arg %d: not as the step kernel's pattern", i);
+        }
+        sa.map_e2n = args[5].map;
+        sa.map_e2c = args[6].map;
+        sa.map_n = args[7].map;
+        sa.map_c = args[8].map;
+        if (sa.dat_q == sa.dat_res) fail(UM_ERR_ARITY, "step kernel: q and res must differ");
+        check_layouts(ctx, {sa.dat_x, sa.dat_q, sa.dat_res, sa.dat_adt}, "step");
+        sa.dtype = check_real(ctx, {sa.dat_x, sa.dat_q, sa.dat_adt}, "step");
     } else {
         fail(UM_ERR_UNSUPPORTED, "unknown kernel %d", kernel);
     }
@@ -162,6 +196,28 @@ void build_host_plan_step(const Ctx &ctx, int32_t kernel, const StepArgs &sa, in
         if (o.block_size % 64) fail(UM_ERR_ARG, "update kernel: block_size must be a multiple of 64");
         hp.n_partials = int32_t((n + o.block_size - 1) / o.block_size);
         if (kernel == UM_K_UPDATE_ADT_2D) hp.emap = ctx.maps[sa.map_n].table;  // [C][4] node ids
+        return;
+    }
+    if (kernel == UM_K_STEP_2D) {
+        if (o.strategy != UM_STRAT_HIER || o.schedule != UM_SCHED_DATAFLOW ||
+            o.gather != UM_GATHER_LDS_DMA || sa.layout != UM_AOS || o.staging != UM_STAGE_ALL)
+            fail(UM_ERR_UNSUPPORTED, "step kernel: HIER plans with the DATAFLOW schedule and the "
+                 "LDS-DMA gather on AoS data only");
+        const Map &me = ctx.maps[sa.map_e2c];
+        const int64_t N = ctx.sets[ctx.dats[sa.dat_x].set].size;
+        if (32 * n > int64_t(INT32_MAX) || 16 * N > int64_t(INT32_MAX))
+            fail(UM_ERR_UNSUPPORTED, "step kernel addresses q and x with 32-bit byte offsets");
+        bool own;
+        hp.blk_off = block_ranges(ctx.sets[me.from], o.block_size, own);
+        EdgeArgs ea;
+        ea.map_n = sa.map_e2n;
+        ea.map_c = sa.map_e2c;
+        ea.dtype = sa.dtype;
+        build_owner_plan(ctx, ea, o, hp, &sa);
+        if (n > 0 && !hp.owner.use)
+            fail(UM_ERR_UNSUPPORTED, "step kernel: the cells' sides are not their edges and "
+                 "boundary edges, or a block stages too many points");
+        hp.n_partials = int32_t(hp.owner.rec.size());
         return;
     }
     // boundary flux: (cell, a, b, 0) per slot

@@ -10,7 +10,9 @@ Marshalling only.  A step is four library loops, enqueued on one stream:
 With build_plans(fuse_adt=True) the update and the next step's adt run as
 one cell loop ("upa", the library's UM_K_UPDATE_ADT_2D): adt is computed
 once before the first step and each step is then flux, bres, upa, with the
-same results bit for bit and one pass over q fewer.
+same results bit for bit and one pass over q fewer.  With a dataflow flux plan
+that gathers by LDS DMA, step() runs flux, bres and upd or upa as one loop (the
+library's UM_K_STEP_2D), equal to rounding.
 
 The mesh may be one mesh or the disjoint union of many (meshgen.union): the
 loops do not care, so a batch of meshes runs as one set of launches.  The
@@ -90,6 +92,7 @@ class TimeStep2D:
             o.coord_map = -1
             U.um_reorder_mesh(ctx, o)
         self.plans: dict[str, Plan] = {}
+        self._whole: Plan | None = None  # edge flux, boundary flux and update as one loop
         if device >= 0:
             self.dev = torch.device("cuda", device)
             self.stream = torch.cuda.current_stream(self.dev).cuda_stream
@@ -222,7 +225,35 @@ class TimeStep2D:
                         [a(self.d_q, -1, 0, U.UM_RW), a(self.d_res, -1, 0, U.UM_RW),
                          a(self.d_adt, -1, 0, U.UM_READ), a(self.d_rms, U.UM_GLOBAL, 0, U.UM_INC)],
                         self.s_cells, self._opts("atomic", cell_block_size), "direct")
+        self._build_whole(dict(block_size=flux_block_size, staging=staging, schedule=schedule,
+                               gather=gather) if flux_strategy == "hier" else {})
         return {k: p.stats for k, p in self.plans.items()}
+
+    def _build_whole(self, flux_opts) -> None:
+        """The step's loops after adt as one loop, where the library has it
+        for the flux plan's options and this mesh."""
+        if self._whole is not None:
+            U.um_plan_destroy(self._whole.handle)
+            self._whole = None
+        if (flux_opts.get("schedule"), flux_opts.get("gather")) != ("dataflow", "lds_dma"):
+            return
+        a = U.um_arg
+        args = [a(self.d_q, -1, 0, U.UM_RW), a(self.d_res, -1, 0, U.UM_RW),
+                a(self.d_adt, -1, 0, U.UM_RW if self.fused else U.UM_READ),
+                a(self.d_rms, U.UM_GLOBAL, 0, U.UM_INC),
+                a(self.d_x, self.m_c2n, U.UM_ALL_SLOTS, U.UM_READ),
+                a(self.d_x, self.m_e2n, U.UM_ALL_SLOTS, U.UM_READ),
+                a(self.d_q, self.m_e2c, U.UM_ALL_SLOTS, U.UM_READ),
+                a(self.d_x, self.m_b2n, U.UM_ALL_SLOTS, U.UM_READ),
+                a(self.d_q, self.m_b2c, 0, U.UM_READ)]
+        o = self._opts("hier", **flux_opts)
+        try:
+            h = U.um_plan_build(self.ctx, U.UM_K_STEP_2D, args, self.s_cells, o)
+        except U.UmeshError as e:
+            if e.status != U.UM_ERR_UNSUPPORTED:
+                raise
+            return
+        self._whole = Plan(h, "hier", o.block_size, U.um_plan_stats_get(h).as_dict())
 
     def flux_args(self):
         a = U.um_arg
@@ -245,6 +276,7 @@ class TimeStep2D:
             U.um_plan_destroy(old.handle)
         self.plans["flux"] = Plan(h, "hier", candidates[best]["block_size"],
                                   U.um_plan_stats_get(h).as_dict())
+        self._build_whole(candidates[best])
         self.res.zero_()
         return best, ms
 
@@ -268,17 +300,30 @@ class TimeStep2D:
 
     def step(self, stream=None) -> None:
         """Enqueue one time step: adt, edge flux, boundary flux, update; with
-        fused plans the adt of a step comes from the previous step's upa
-        (computed here only before the first step, or after invalidate_adt)."""
-        if not self.fused:
-            for name in ("adt", "flux", "bres", "upd"):
-                self.run_loop(name, stream)
-            return
-        if not self.adt_valid:
+        fused plans the adt of a step comes from the previous step's update
+        (computed here only before the first step, or after invalidate_adt).
+        With a dataflow flux plan that gathers by LDS DMA the loops after adt
+        run as one (UM_K_STEP_2D); the results are those of the separate
+        loops, to rounding."""
+        if not self.fused or not self.adt_valid:
             self.run_loop("adt", stream)
-        for name in ("flux", "bres", "upa"):
-            self.run_loop(name, stream)
-        self.adt_valid = True
+        if self._whole is not None:
+            U.um_loop_exec(self._whole.handle, self.params("bres"),
+                           self.stream if stream is None else stream)
+        else:
+            for name in ("flux", "bres", "upa" if self.fused else "upd"):
+                self.run_loop(name, stream)
+        self.adt_valid = self.fused
+
+    def step_launches(self) -> int:
+        """Kernel launches of one step (with fused plans, of one whose adt is
+        the previous step's)."""
+        if self._whole is not None:
+            n = self._whole.stats["n_launches"]
+        else:
+            n = sum(self.plans[k].stats["n_launches"]
+                    for k in ("flux", "bres", "upa" if self.fused else "upd"))
+        return n + (0 if self.fused else self.plans["adt"].stats["n_launches"])
 
     def close(self) -> None:
         if self.ctx:

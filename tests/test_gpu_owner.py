@@ -18,6 +18,7 @@ from oracle import native  # noqa: E402
 from paper_1802_03749_amd import umesh as U  # noqa: E402
 from paper_1802_03749_amd.edgeloop import EdgeFluxLoop  # noqa: E402
 from paper_1802_03749_amd.hexloop import HexLoop  # noqa: E402
+from paper_1802_03749_amd.timestep import TimeStep2D  # noqa: E402
 
 
 def rel_l2(a, b):
@@ -127,3 +128,62 @@ def test_non_finite_states_stay_with_their_neighbours():
     assert np.array_equal(np.isfinite(out[0]), np.isfinite(out[1]))
     fine = np.isfinite(out[0])
     assert 0 < (~fine).sum() <= 40 and rel_l2(out[0][fine], out[1][fine]) <= 1e-12
+
+
+QINF = np.array([1.0, 0.35, 0.05, 2.7])
+
+
+@pytest.mark.parametrize("fuse", [True, False])
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+@pytest.mark.parametrize("nx,ny,S,points", [(150, 70, 512, 2), (37, 53, 64, 0), (2, 1, 64, 1),
+                                            (61, 260, 1024, 2)])
+def test_whole_step(nx, ny, S, points, dtype, fuse):
+    """Edge flux, boundary flux and update as one loop against the separate
+    loops from the same state: two steps, the first with residuals that hold
+    something.  Bars: binary64 1e-12; binary32 q and adt 4 ulp of 6e-8."""
+    m = quad_mesh(nx, ny, seed=11)
+    start = np.random.default_rng(1).uniform(-1e-2, 1e-2, (nx * ny, 4))
+    T = []
+    for whole in (True, False):
+        t = TimeStep2D(m.x, m.q, m.e2n, m.e2c, m.b2n, m.b2c, m.c2n, QINF, device=0, block_size=S,
+                       point_reorder=points, dtype=dtype)
+        t.build_plans(flux_block_size=S, schedule="dataflow", gather="lds_dma",
+                      elems_per_thread=2, fuse_adt=fuse)
+        assert t._whole is not None
+        if not whole:
+            t._whole = None
+        t.res.copy_(torch.from_numpy(start))
+        T.append(t)
+    for k in (1, 2):
+        for t in T:
+            t.step()
+        torch.cuda.synchronize()
+        a, b = T
+        bar = 1e-12 if dtype == "f64" else 2.4e-7
+        assert rel_l2(a.q_user(), b.q_user()) <= bar
+        assert rel_l2(a.adt_user(), b.adt_user()) <= bar
+        assert not a.res.view(torch.int64).any() and not b.res.any()
+        assert abs(a.rms.item() - b.rms.item()) <= (1e-12 if dtype == "f64" else 1e-6) * b.rms.item()
+    for t in T:
+        t.close()
+
+
+def test_whole_step_in_a_graph():
+    """Replays of a captured step against eager steps."""
+    m = quad_mesh(200, 90, seed=12)
+    T = [TimeStep2D(m.x, m.q, m.e2n, m.e2c, m.b2n, m.b2c, m.c2n, QINF, device=0,
+                    block_size=256) for _ in range(2)]
+    for t in T:
+        t.build_plans(flux_block_size=256, schedule="dataflow", gather="lds_dma",
+                      elems_per_thread=2, fuse_adt=True)
+        t.step()
+    g = U.HipGraph(T[0].step)
+    for k in range(4):
+        g.replay()
+        T[1].step()
+        torch.cuda.synchronize()
+        assert torch.equal(T[0].q, T[1].q) and torch.equal(T[0].adt, T[1].adt)
+        assert T[0].rms.item() == T[1].rms.item()
+    g.close()
+    for t in T:
+        t.close()

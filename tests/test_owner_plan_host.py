@@ -9,6 +9,7 @@ from meshgen import hex_mesh, quad_mesh
 from paper_1802_03749_amd import umesh as U
 from paper_1802_03749_amd.edgeloop import EdgeFluxLoop
 from paper_1802_03749_amd.hexloop import HexLoop
+from paper_1802_03749_amd.timestep import TimeStep2D
 
 
 def tiles(m, tx, ty):
@@ -154,3 +155,69 @@ def test_hex_owned_nodes_and_their_elements(n, S, explicit, points):
         at += n_own
     assert row == rows and at == counts.size and np.all(seen == 1)
     L.close()
+
+
+def step(m, **kw):
+    T = TimeStep2D(m.x, m.q, m.e2n, m.e2c, m.b2n, m.b2c, m.c2n, [1.0, 0.35, 0.05, 2.7],
+                   device=-1, block_size=64, **kw)
+    T.build_plans(flux_block_size=64, schedule="dataflow", gather="lds_dma", elems_per_thread=2)
+    return T
+
+
+@pytest.mark.parametrize("points", [0, 2])
+@pytest.mark.parametrize("nx,ny", [(23, 17), (2, 1), (5, 1)])
+def test_step_plan_has_every_side_of_every_cell(nx, ny, points):
+    """The step's plan owns every cell; side k of a cell runs from node k to
+    node k + 1 of its row and has the edge or boundary edge that lies there."""
+    m = quad_mesh(nx, ny, seed=8)
+    T = step(m, point_reorder=points)
+    h = T._whole.handle
+    get = lambda f: (lambda out: (U.um_plan_export(h, f, out, out.size), out)[1])(
+        np.empty(U.um_plan_export(h, f), np.int32))
+    table = lambda mp, k: (lambda out: (U.um_get_map(T.ctx, mp, out), out)[1])(
+        np.empty((k, {T.m_c2n: 4, T.m_b2c: 1}.get(mp, 2)), np.int32))
+    rec = get(U.UM_EXP_OWNER_RECORDS).reshape(-1, 10)
+    ids = get(U.UM_EXP_OWNER_IDS).reshape(rec.shape[0], -1)
+    sides = get(U.UM_EXP_OWNER_SIDES).reshape(-1, 4, 4)
+    c2n = table(T.m_c2n, T.C)
+    out = {}  # (cell, a, b) -> neighbour
+    for (l, r), (a, b) in zip(table(T.m_e2c, T.E).tolist(), table(T.m_e2n, T.E).tolist()):
+        out[l, a, b] = (r, 0)
+        out[r, b, a] = (l, 1)
+    for (c,), (a, b) in zip(table(T.m_b2c, T.B).tolist(), table(T.m_b2n, T.B).tolist()):
+        out[c, a, b] = (-2, 0)
+    seen, row = [], 0
+    for (_, n_own, nc, nn, c0, c_run, n0, n_run, node_item, n_items), it in zip(rec, ids):
+        assert c_run <= n_own <= nc <= 1022 and nn <= 1022
+        cells = np.concatenate([np.arange(c0, c0 + c_run), it[:nc - c_run]])
+        nodes = np.concatenate([np.arange(n0, n0 + n_run), it[node_item:n_items]])
+        for i in range(n_own):
+            c = int(cells[i])
+            seen.append(c)
+            for k in range(4):
+                h, a, b, slot = sides[row + i, k]
+                want = out[c, int(c2n[c, k]), int(c2n[c, (k + 1) % 4])]
+                assert (nodes[a], nodes[b]) == (c2n[c, k], c2n[c, (k + 1) % 4])
+                assert ((int(cells[h]) if h >= 0 else int(h)), int(slot)) == want
+        row += n_own
+    assert sorted(seen) == list(range(T.C))
+    assert T.step_launches() == 3
+    T.close()
+
+
+def test_step_plan_refused():
+    """A boundary edge that runs the other way round, a second one on the same
+    side, an edge between nodes that no side joins, and a cell without an
+    edge: the loops run separately."""
+    m = quad_mesh(6, 5, seed=8)
+    m.b2n[3] = m.b2n[3, ::-1]
+    T = step(m)
+    assert T._whole is None and T.step_launches() > 3
+    T.close()
+    m = quad_mesh(6, 5, seed=8)
+    m.b2n, m.b2c = np.concatenate([m.b2n, m.b2n[:1]]), np.concatenate([m.b2c, m.b2c[:1]])
+    assert step(m)._whole is None
+    m = quad_mesh(6, 5, seed=8)
+    m.e2n[7, 0] = m.e2n[8, 1]
+    assert step(m)._whole is None
+    assert step(quad_mesh(1, 1, seed=8))._whole is None
