@@ -105,7 +105,8 @@ typedef enum { UM_TC_BARRIER = 0, UM_TC_LDS_ATOMIC = 1 } um_tcmode;
  * deterministic, bounded to 100 moves per block) for one colour fewer at a
  * time; the plan keeps the fewest colours found.  Slower to build. */
 typedef enum { UM_BCOL_FIRST_FIT = 0, UM_BCOL_RECOLOUR = 1, UM_BCOL_MIN = 2 } um_bcolouring;
-/* How block colours are ordered in time (HIER).  COLOUR_LAUNCHES: one kernel
+/* How block colours are ordered in time (HIER), where an order is needed (see
+ * below).  COLOUR_LAUNCHES: one kernel
  * launch per block colour (the kernel boundary orders colours, Section 2.2).
  * DATAFLOW: one launch over all blocks in colour order; each block computes
  * its fluxes, then waits until every neighbouring block of an earlier colour
@@ -122,13 +123,15 @@ typedef enum { UM_BCOL_FIRST_FIT = 0, UM_BCOL_RECOLOUR = 1, UM_BCOL_MIN = 2 } um
  * completed (all flags advance together), so the launch needs no host-side
  * counter and may be captured in a HIP graph and replayed.  Supported for STAGE_ALL with one or two
  * elements per lane; a plan must not execute concurrently with itself.
- * Plans of the hex loop, and of the edge loop with the LDS-DMA gather or SoA
- * data (binary32: at two elements per lane), need no order between blocks where no cell has more than 8 edges (no
- * node more than 16 elements), no block stages more than 1023 points of a
- * set and the hex loop has at most 2,000,000 elements: they run the owner kernels, in which each point is incremented by
- * one of its blocks only, which evaluates all elements around it, those on
- * its border too.  Such a launch has no waits, no flags and no colour
- * rounds; its results are reproducible bit for bit in every um_tcmode.  The block and thread colours, the launch
+ * Of either schedule, STAGE_ALL plans need no order between blocks where no
+ * cell has more than 8 edges (no node more than 16 elements), no block stages
+ * more than 1023 points of a set and q, x and force stay below 2^31 bytes:
+ * they run the owner kernels, in which each point is incremented by one of
+ * its blocks only, which evaluates all elements around it, those on its
+ * border too.  DATAFLOW plans do so with the LDS-DMA gather or SoA data
+ * (binary32: at two elements per lane), of the hex loop with at most
+ * 2,000,000 elements.  Such a plan is one launch, without waits, flags and
+ * colour rounds; its results are reproducible bit for bit in every um_tcmode.  The block and thread colours, the launch
  * order by colour and the statistics below describe the plan's blocks all
  * the same. */
 typedef enum { UM_SCHED_COLOUR_LAUNCHES = 0, UM_SCHED_DATAFLOW = 1 } um_schedule;
@@ -252,8 +255,9 @@ typedef enum { UM_GATHER_REGISTERS = 0, UM_GATHER_LDS_DMA = 1 } um_gather;
  *   7: x   via the boundary-edge->node map (arity 2), UM_READ
  *   8: q   via the boundary-edge->cell map (arity 1) slot 0, UM_READ
  * (4 to 7 with idx UM_ALL_SLOTS).  params = {gm1, eps, qinf0..3}.  AoS data;
- * options as for an edge-flux plan, HIER with the DATAFLOW schedule and the
- * LDS-DMA gather.  Every side of a cell (from node k to node k + 1 of its
+ * options as for an edge-flux plan, HIER with STAGE_ALL staging and the
+ * DATAFLOW schedule with the LDS-DMA gather, or COLOUR_LAUNCHES (they differ
+ * in the rounding of binary32 fluxes, as the edge-flux plans do).  Every side of a cell (from node k to node k + 1 of its
  * row) must be one edge's or boundary edge's, with the normal pointing out
  * of the edge's first cell, or nobody's, and every cell needs an edge:
  * UM_ERR_UNSUPPORTED otherwise.  Results as of the separate loops, to

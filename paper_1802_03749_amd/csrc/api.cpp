@@ -49,6 +49,27 @@ struct DeviceGuard {
     }
 };
 
+// Edge plans that the owner kernel takes over: those of the colour launches
+// (the drivers' default) and of the dataflow schedule wherever its binary32
+// results are the same bit for bit.  A chain of block colours costs 6 us a
+// colour as launches and 3 to 5 as flags (600x300 cells, binary64: 29.8 us in
+// five launches, 7.9 as one of the owner kernel; 90x70: 23.4 -> 4.0); the colours
+// read the staged cells once each, so it gains at 2400x1200 cells too, 103.3 ->
+// 71.4 (binary32 90.5 -> 61.7).  Not taken: dataflow plans of SoA binary32 data at
+// one edge per lane, whose kernel rounds by itself (1.2e-7 from the others), and
+// the register gather on AoS data, which names the waiting kernel where the
+// LDS-DMA gather is there for speed.  The owner kernel addresses q and x with
+// 32-bit byte offsets.
+bool owner_kernel_for(const Ctx &c, const EdgeArgs &ea, const um_plan_opts &o,
+                      const HostPlan &hp) {
+    if (hp.strategy != UM_STRAT_HIER || hp.staging != UM_STAGE_ALL) return false;
+    const int64_t C = c.sets[c.maps[ea.map_c].to].size, N = c.sets[c.maps[ea.map_n].to].size;
+    if (32 * C > int64_t(INT32_MAX) || 16 * N > int64_t(INT32_MAX)) return false;
+    if (o.schedule == UM_SCHED_COLOUR_LAUNCHES) return true;
+    if (ea.layout == UM_SOA) return ea.dtype == UM_F64 || hp.ept == 2;
+    return o.gather == UM_GATHER_LDS_DMA;
+}
+
 template <typename F>
 um_status guarded(F &&f) {
     try {
@@ -308,6 +329,7 @@ LaunchArgs launch_args_step(Plan &p, const double *params, int32_t nparams, void
     la.stream = static_cast<hipStream_t>(stream);
     la.layout = p.sa.layout;
     la.dtype = p.sa.dtype;
+    la.schedule = p.hp.schedule;
     la.block_size = p.hp.block_size;
     la.emap = p.dp.emap;
     const StepArgs &sa = p.sa;
@@ -678,14 +700,7 @@ um_status um_plan_build(um_ctx ctx, int32_t kernel, const um_arg *args, int32_t 
                          "LDS-DMA gather: HIER plans with the DATAFLOW schedule on AoS data only");
                 build_host_plan(c, p->ea, iter_set, o, p->hp);
                 p->hp.gather = o.gather;
-                // The owner kernel rounds binary32 fluxes as the waiting kernels
-                // do; of those, the SoA one at one edge per lane rounds by
-                // itself (1.2e-7 from the others) and keeps its plans.  The
-                // register gather on AoS data is the waiting kernel by choice:
-                // AoS plans have the LDS-DMA gather for speed.
-                if (p->hp.strategy == UM_STRAT_HIER && p->hp.schedule == UM_SCHED_DATAFLOW &&
-                    (p->ea.layout == UM_SOA ? p->ea.dtype == UM_F64 || p->hp.ept == 2
-                                            : o.gather == UM_GATHER_LDS_DMA))
+                if (owner_kernel_for(c, p->ea, o, p->hp))
                     build_owner_plan(c, p->ea, o, p->hp);
             } else if (is_step_kernel(kernel)) {
                 if (o.gather != UM_GATHER_REGISTERS && kernel != UM_K_STEP_2D)
@@ -697,7 +712,8 @@ um_status um_plan_build(um_ctx ctx, int32_t kernel, const um_arg *args, int32_t 
                     fail(UM_ERR_UNSUPPORTED, "LDS-DMA gather: edge flux loop only");
                 p->ha = check_hex_args(c, args, nargs, iter_set);
                 build_host_plan_hex(c, p->ha, iter_set, o, p->hp);
-                if (p->hp.strategy == UM_STRAT_HIER && p->hp.schedule == UM_SCHED_DATAFLOW)
+                if (p->hp.strategy == UM_STRAT_HIER && 24 * c.sets[c.maps[p->ha.map].to].size <=
+                                                           int64_t(INT32_MAX))
                     build_owner_plan_hex(c, p->ha, o, p->hp);
             }
             if (c.device >= 0) {
@@ -786,7 +802,8 @@ um_status um_plan_stats_get(um_plan plan, um_plan_stats *out) {
             out->n_launches = 0;
             for (int32_t c = 0; c + 1 < int32_t(hp.bcol_off.size()); ++c)
                 out->n_launches += hp.bcol_off[c + 1] > hp.bcol_off[c];
-            if (hp.schedule == UM_SCHED_DATAFLOW) out->n_launches = out->n_launches > 0;
+            if (hp.schedule == UM_SCHED_DATAFLOW || hp.owner.use)
+                out->n_launches = out->n_launches > 0;
         } else if (hp.strategy == UM_STRAT_GLOBAL_COLOUR) {
             out->n_global_colours = int32_t(hp.colour_off.size()) - 1;
             out->n_launches = out->n_global_colours;
@@ -1090,12 +1107,11 @@ void exec_plan(Plan &p, const double *params, int32_t nparams, void *stream, boo
             } else {
                 step(LAUNCH_ATOMIC, 0, n);
             }
+        } else if (hp.owner.use) {
+            one(LAUNCH_OWNER, 0, int32_t(hp.owner.rec.size()), hp.owner.lds);
         } else if (hp.strategy == UM_STRAT_HIER && hp.schedule == UM_SCHED_DATAFLOW) {
             // the execution number is kept and advanced on the device
-            if (hp.owner.use)
-                one(LAUNCH_OWNER, 0, int32_t(hp.owner.rec.size()), hp.owner.lds);
-            else
-                one(LAUNCH_HIER_FLOW, 0, int32_t(hp.blk_order.size()), hp.lds_max);
+            one(LAUNCH_HIER_FLOW, 0, int32_t(hp.blk_order.size()), hp.lds_max);
         } else if (hp.strategy == UM_STRAT_HIER) {
             for (int32_t c = 0; c + 1 < int32_t(hp.bcol_off.size()); ++c)
                 if (hp.bcol_off[c + 1] > hp.bcol_off[c])
@@ -1187,7 +1203,13 @@ um_status um_plan_autotune(um_ctx ctx, int32_t kernel, const um_arg *args, int32
                         continue;
                     }
                     if (ms_out) ms_out[i] = per;
-                    if (!best || per < best_ms) {
+                    // Owner plans over the same blocks are one kernel; of those
+                    // the dataflow schedule's stays, so that the choice (and
+                    // with it the rounding of binary32 fluxes) does not hang on
+                    // the timer.
+                    const bool same = best && best->hp.owner.use && p->hp.owner.use &&
+                                      best->hp.blk_off == p->hp.blk_off;
+                    if (!best || (same ? best->hp.schedule < p->hp.schedule : per < best_ms)) {
                         if (best) um_plan_destroy(best);
                         best = p;
                         best_ms = per;

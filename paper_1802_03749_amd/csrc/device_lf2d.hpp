@@ -85,7 +85,7 @@ __device__ __forceinline__ Flow<Real> flow_of(const Real q[4], Real gm1) {
 // that the cell left is the edge's second one.  Seen from the other side
 // (states swapped, a and b swapped, second inverted) it is exactly the
 // negative: every value rounded only changes its sign.
-template <bool SOA, typename Real>
+template <bool DISS, typename Real>
 __device__ __forceinline__ void lf2d_flux_out(Real xa0, Real xa1, Real xb0, Real xb1,
                                               const Real q[4], const Flow<Real> &s,
                                               const Real r[4], const Flow<Real> &t, Real aq,
@@ -110,9 +110,10 @@ __device__ __forceinline__ void lf2d_flux_out(Real xa0, Real xa1, Real xb0, Real
     F[2] = fma(s.p, ny, q[2] * U) + fma(t.p, ny, r[2] * V);
 #pragma unroll
     for (int k = 0; k < 4; ++k) f[k] = fma(q[k] - r[k], hm, half * F[k]);
-    if constexpr (SOA && sizeof(Real) == 4) {
-        // there (hier_flow_kernel, two edges per lane) the compiler rounds
-        // the dissipation of these two components first
+    if constexpr (DISS && sizeof(Real) == 4) {
+        // in hier_kernel, and in hier_flow_kernel on SoA data at two edges per
+        // lane, the compiler rounds the dissipation of these two components
+        // first
         f[0] = fma(half, F[0], (q[0] - r[0]) * hm);
         f[3] = fma(half, F[3], (q[3] - r[3]) * hm);
     }

@@ -979,7 +979,7 @@ struct StepOut {
     double qinf[4];
 };
 
-template <int LAYOUT, bool RING, int STEP, typename Real>
+template <int LAYOUT, bool RING, bool DISS, int STEP, typename Real>
 __device__ __forceinline__ void owner_block(const OwnRec *__restrict__ recs,
                                             const int32_t *__restrict__ ids, int32_t id_stride,
                                             const uint32_t *__restrict__ words, int32_t quads,
@@ -1128,7 +1128,7 @@ __device__ __forceinline__ void owner_block(const OwnRec *__restrict__ recs,
             Real qh[4], ah, f[4];
             state(h, qh, ah);
             if (STEP != FLUX_ONLY && h == nc) ah = a;
-            dev::lf2d_flux_out<LAYOUT == UM_SOA>(xa0, xa1, xb0, xb1, q, own, qh,
+            dev::lf2d_flux_out<DISS>(xa0, xa1, xb0, xb1, q, own, qh,
                                                  dev::flow_of(qh, gm1), a, ah, eps, second, f);
 #pragma unroll
             for (int c = 0; c < 4; ++c) r[c] += double(f[c]);
@@ -1217,14 +1217,15 @@ __device__ __forceinline__ void owner_block(const OwnRec *__restrict__ recs,
     }
 }
 
-template <int LAYOUT, bool RING, typename Real>
+template <int LAYOUT, bool RING, bool DISS, typename Real>
 __global__ __launch_bounds__(1024) void owner_kernel(const OwnRec *__restrict__ recs,
                                                      const int32_t *__restrict__ ids,
                                                      int32_t id_stride,
                                                      const uint32_t *__restrict__ words,
                                                      int32_t quads, Dats<Real> d, double gm1,
                                                      double eps) {
-    owner_block<LAYOUT, RING, FLUX_ONLY, Real>(recs, ids, id_stride, words, quads, d, gm1, eps, {});
+    owner_block<LAYOUT, RING, DISS, FLUX_ONLY, Real>(recs, ids, id_stride, words, quads, d, gm1,
+                                                     eps, {});
 }
 
 // A time step's edge flux, boundary flux and update (with NEW_ADT also the
@@ -1238,14 +1239,14 @@ __global__ __launch_bounds__(1024) void owner_kernel(const OwnRec *__restrict__ 
 // owner_kernel: the update's divisions and the square roots of adt double the
 // arithmetic (8.7 instead of 4.6 million vector instructions).  Writing every
 // cell's next state to a buffer and copying it back took 41.6 us in all.
-template <int STEP, typename Real>
+template <int STEP, bool DISS, typename Real>
 __global__ __launch_bounds__(1024) void step_kernel(const OwnRec *__restrict__ recs,
                                                     const int32_t *__restrict__ ids,
                                                     int32_t id_stride,
                                                     const uint32_t *__restrict__ words,
                                                     Dats<Real> d, double gm1, double eps,
                                                     StepOut<Real> out) {
-    owner_block<UM_AOS, true, STEP, Real>(recs, ids, id_stride, words, 1, d, gm1, eps, out);
+    owner_block<UM_AOS, true, DISS, STEP, Real>(recs, ids, id_stride, words, 1, d, gm1, eps, out);
 }
 
 // Workgroup 0 adds the partial sums in a fixed order to the global target;
@@ -1421,16 +1422,32 @@ hipError_t launch_flow(const LaunchArgs &la, int32_t nblocks, int64_t lds, const
     return hipErrorInvalidValue;
 }
 
-template <int LAYOUT, bool RING, typename Real>
-hipError_t launch_owner(const LaunchArgs &la, int32_t nblocks, int64_t lds, const Dats<Real> &d) {
+template <int LAYOUT, bool RING, bool DISS, typename Real>
+hipError_t launch_owner_one(const LaunchArgs &la, int32_t nblocks, int64_t lds,
+                            const Dats<Real> &d) {
     clear_stale_error();
     const hipError_t ea =
-        allow_lds(reinterpret_cast<const void *>(owner_kernel<LAYOUT, RING, Real>), lds);
+        allow_lds(reinterpret_cast<const void *>(owner_kernel<LAYOUT, RING, DISS, Real>), lds);
     if (ea != hipSuccess) return ea;
-    hipLaunchKernelGGL((owner_kernel<LAYOUT, RING, Real>), dim3(nblocks), dim3(la.own_threads),
+    hipLaunchKernelGGL((owner_kernel<LAYOUT, RING, DISS, Real>), dim3(nblocks), dim3(la.own_threads),
                        size_t(lds), la.stream, la.own_rec, la.own_ids, la.own_stride,
                        la.own_words, la.own_quads, d, la.gm1, la.eps);
     return hipGetLastError();
+}
+
+// Binary32 results keep the rounding of the plan's waiting or colour kernel
+// (lf2d_flux_out); binary64 has one form.
+template <int LAYOUT, typename Real>
+hipError_t launch_owner(const LaunchArgs &la, int32_t nblocks, int64_t lds, const Dats<Real> &d) {
+    if constexpr (sizeof(Real) == 4) {
+        if (LAYOUT == UM_SOA || la.schedule == UM_SCHED_COLOUR_LAUNCHES)
+            return la.own_quads == 0 ? launch_owner_one<LAYOUT, true, true>(la, nblocks, lds, d)
+                                     : launch_owner_one<LAYOUT, false, true>(la, nblocks, lds, d);
+    }
+    if constexpr (sizeof(Real) == 8 || LAYOUT == UM_AOS)
+        return la.own_quads == 0 ? launch_owner_one<LAYOUT, true, false>(la, nblocks, lds, d)
+                                 : launch_owner_one<LAYOUT, false, false>(la, nblocks, lds, d);
+    return hipErrorInvalidValue;
 }
 
 template <int LAYOUT, typename Real>
@@ -1439,8 +1456,7 @@ hipError_t launch_typed(const LaunchArgs &la, int which, int32_t begin, int32_t 
                        static_cast<const Real *>(la.adt), la.res, la.N, la.C};
     if (which == LAUNCH_HIER) return launch_hier<LAYOUT>(la, end - begin, begin, lds, d);
     if (which == LAUNCH_OWNER)
-        return la.own_quads == 0 ? launch_owner<LAYOUT, true>(la, end - begin, lds, d)
-                                 : launch_owner<LAYOUT, false>(la, end - begin, lds, d);
+        return launch_owner<LAYOUT>(la, end - begin, lds, d);
     if (which == LAUNCH_HIER_FLOW) {
         if (la.staging != UM_STAGE_ALL || (la.ept != 1 && la.ept != 2) || end - begin <= 0)
             return hipErrorInvalidValue;
@@ -1493,7 +1509,12 @@ hipError_t step2d_typed(const LaunchArgs &la, int which, int32_t begin, int32_t 
         const StepOut<Real> out{q, adt, static_cast<Real *>(la.new_q),
                                 static_cast<Real *>(la.new_adt), la.partials,
                                 {la.qinf[0], la.qinf[1], la.qinf[2], la.qinf[3]}};
-        auto kern = la.keeps_adt ? step_kernel<STEP_KEEP_ADT, Real> : step_kernel<STEP_NEW_ADT, Real>;
+        auto kern = la.keeps_adt ? step_kernel<STEP_KEEP_ADT, false, Real>
+                                 : step_kernel<STEP_NEW_ADT, false, Real>;
+        if constexpr (sizeof(Real) == 4)  // as in launch_owner
+            if (la.schedule == UM_SCHED_COLOUR_LAUNCHES)
+                kern = la.keeps_adt ? step_kernel<STEP_KEEP_ADT, true, Real>
+                                    : step_kernel<STEP_NEW_ADT, true, Real>;
         const hipError_t ea = allow_lds(reinterpret_cast<const void *>(kern), lds);
         if (ea != hipSuccess) return ea;
         hipLaunchKernelGGL(kern, dim3(end - begin), dim3(la.own_threads), size_t(lds), la.stream,

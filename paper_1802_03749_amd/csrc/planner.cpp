@@ -538,16 +538,18 @@ void build_host_plan(const Ctx &ctx, const EdgeArgs &ea, int32_t iter_set,
         bi.cell_off = int32_t(hp.stg_c.size());
         bi.node_off = int32_t(hp.stg_n.size());
         const size_t c0 = hp.stg_c.size(), n0 = hp.stg_n.size();
-        for (int32_t e = e0; e < e1; ++e) {
-            hp.stg_c.push_back(mc.table[2 * int64_t(e)]);
-            hp.stg_c.push_back(mc.table[2 * int64_t(e) + 1]);
-            hp.stg_n.push_back(mn.table[2 * int64_t(e)]);
-            hp.stg_n.push_back(mn.table[2 * int64_t(e) + 1]);
+        // each point once, then sorted: a quarter of the slots to sort
+        auto first_seen = [](int32_t point, std::vector<int32_t> &loc, std::vector<int32_t> &list) {
+            if (loc[point] >= 0) return;
+            loc[point] = 0;
+            list.push_back(point);
+        };
+        for (int64_t i = 2 * int64_t(e0); i < 2 * int64_t(e1); ++i) {
+            first_seen(mc.table[i], cloc, hp.stg_c);
+            first_seen(mn.table[i], nloc, hp.stg_n);
         }
         std::sort(hp.stg_c.begin() + c0, hp.stg_c.end());
-        hp.stg_c.erase(std::unique(hp.stg_c.begin() + c0, hp.stg_c.end()), hp.stg_c.end());
         std::sort(hp.stg_n.begin() + n0, hp.stg_n.end());
-        hp.stg_n.erase(std::unique(hp.stg_n.begin() + n0, hp.stg_n.end()), hp.stg_n.end());
         const int32_t nc = int32_t(hp.stg_c.size() - c0), nn = int32_t(hp.stg_n.size() - n0);
         for (int32_t i = 0; i < nc; ++i) cloc[hp.stg_c[c0 + i]] = i;
         for (int32_t i = 0; i < nn; ++i) nloc[hp.stg_n[n0 + i]] = i;

@@ -457,7 +457,9 @@ void build_owner_plan_hex(const Ctx &ctx, const HexArgs &ha, const um_plan_opts 
     // are not.  One sweep, waiting -> owner kernel: 24^3 elements 22.5 -> 5.7
     // us, 64^3 39.0 -> 11.9, 96^3 58.3 -> 34.5 (49.9 with MIN colouring), 120^3
     // 80.9 -> 70.4, but 128^3 73.4 -> 75.5 and, with LDS atomics, 67.8 -> 75.6.
-    if (nb <= 0 || E > 2000000) return;
+    // As launches the colours cost more at every size: 24^3 54.4 -> 6.0, 96^3
+    // 117.1 -> 34.8, 128^3 121.0 -> 75.2, 160^3 260 -> 175.
+    if (nb <= 0 || (o.schedule == UM_SCHED_DATAFLOW && E > 2000000)) return;
     Around ar;
     if (!ar.build(m, N, hp.blk_off, {8, MAX_NODE_ELEMENTS})) return;
     const auto &[D, own_off, own, inc, deg, owner] = ar;

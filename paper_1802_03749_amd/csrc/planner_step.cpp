@@ -199,10 +199,11 @@ void build_host_plan_step(const Ctx &ctx, int32_t kernel, const StepArgs &sa, in
         return;
     }
     if (kernel == UM_K_STEP_2D) {
-        if (o.strategy != UM_STRAT_HIER || o.schedule != UM_SCHED_DATAFLOW ||
-            o.gather != UM_GATHER_LDS_DMA || sa.layout != UM_AOS || o.staging != UM_STAGE_ALL)
-            fail(UM_ERR_UNSUPPORTED, "step kernel: HIER plans with the DATAFLOW schedule and the "
-                 "LDS-DMA gather on AoS data only");
+        if (o.strategy != UM_STRAT_HIER || sa.layout != UM_AOS || o.staging != UM_STAGE_ALL ||
+            (o.schedule == UM_SCHED_DATAFLOW) != (o.gather == UM_GATHER_LDS_DMA))
+            fail(UM_ERR_UNSUPPORTED, "step kernel: HIER plans with STAGE_ALL staging on AoS data, "
+                 "with the DATAFLOW schedule and the LDS-DMA gather or with colour launches");
+        hp.schedule = o.schedule;  // the rounding of binary32 fluxes
         const Map &me = ctx.maps[sa.map_e2c];
         const int64_t N = ctx.sets[ctx.dats[sa.dat_x].set].size;
         if (32 * n > int64_t(INT32_MAX) || 16 * N > int64_t(INT32_MAX))

@@ -235,7 +235,9 @@ class TimeStep2D:
         if self._whole is not None:
             U.um_plan_destroy(self._whole.handle)
             self._whole = None
-        if (flux_opts.get("schedule"), flux_opts.get("gather")) != ("dataflow", "lds_dma"):
+        # the register gather of a dataflow plan asks for that plan's own kernel
+        if not flux_opts or (flux_opts.get("schedule") == "dataflow" and
+                             flux_opts.get("gather") != "lds_dma"):
             return
         a = U.um_arg
         args = [a(self.d_q, -1, 0, U.UM_RW), a(self.d_res, -1, 0, U.UM_RW),
@@ -302,9 +304,9 @@ class TimeStep2D:
         """Enqueue one time step: adt, edge flux, boundary flux, update; with
         fused plans the adt of a step comes from the previous step's update
         (computed here only before the first step, or after invalidate_adt).
-        With a dataflow flux plan that gathers by LDS DMA the loops after adt
-        run as one (UM_K_STEP_2D); the results are those of the separate
-        loops, to rounding."""
+        With a flux plan of colour launches, or a dataflow one that gathers by
+        LDS DMA, the loops after adt run as one (UM_K_STEP_2D) where the mesh
+        allows it; the results are those of the separate loops, to rounding."""
         if not self.fused or not self.adt_valid:
             self.run_loop("adt", stream)
         if self._whole is not None:

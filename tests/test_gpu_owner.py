@@ -42,12 +42,14 @@ def random_cells(C, sides, seed):
 def check(mesh, dtype, layout, **kw):
     x, q, adt, e2n, e2c = mesh
     L = EdgeFluxLoop(x, q, adt, e2n, e2c, device=0, layout=layout, dtype=dtype, **kw.pop("loop"))
-    p = L.plan("hier", L.part_block_size or kw.pop("S"), schedule="dataflow", elems_per_thread=2,
-               gather="lds_dma" if layout == "aos" else "registers", **kw)
-    assert L.export(p, U.UM_EXP_OWNER_RECORDS).size
-    sides = L.export(p, U.UM_EXP_OWNER_SIDES)
-    for k in (1, 2):
+    S = L.part_block_size or kw.pop("S")
+    for flow in (False, True):  # one sweep each
+        p = L.plan("hier", S, **(dict(schedule="dataflow", elems_per_thread=2,
+                                      gather="lds_dma" if layout == "aos" else "registers")
+                                 if flow else {}), **kw)
+        assert p.stats["n_launches"] == 1 and L.export(p, U.UM_EXP_OWNER_RECORDS).size
         L.run(p)
+    sides = L.export(p, U.UM_EXP_OWNER_SIDES)
     torch.cuda.synchronize()
     if dtype == "f64":
         assert rel_l2(L.res_user(), 2 * native.edge_loop(e2n, e2c, x, q, adt)) <= 1e-12
@@ -80,9 +82,9 @@ def test_other_cells(sides, layout, dtype):
 
 def check_hex(x, v, e2n, layout, loop, S, **kw):
     L = HexLoop(x, v, e2n, device=0, layout=layout, **loop)
-    p = L.plan("hier", S, schedule="dataflow", block_colouring="recolour", **kw)
-    assert L.export(p, U.UM_EXP_OWNER_RECORDS).size
-    for k in (1, 2):
+    for schedule in ("dataflow", "colour_launches"):  # one sweep each
+        p = L.plan("hier", S, schedule=schedule, block_colouring="recolour", **kw)
+        assert p.stats["n_launches"] == 1 and L.export(p, U.UM_EXP_OWNER_RECORDS).size
         L.run(p)
     torch.cuda.synchronize()
     assert rel_l2(L.force_user(), 2 * native.hex_loop(e2n, x, v)) <= 1e-12
@@ -133,11 +135,13 @@ def test_non_finite_states_stay_with_their_neighbours():
 QINF = np.array([1.0, 0.35, 0.05, 2.7])
 
 
+@pytest.mark.parametrize("opts", [dict(schedule="dataflow", gather="lds_dma", elems_per_thread=2),
+                                  dict()], ids=["dataflow", "default"])
 @pytest.mark.parametrize("fuse", [True, False])
 @pytest.mark.parametrize("dtype", ["f64", "f32"])
 @pytest.mark.parametrize("nx,ny,S,points", [(150, 70, 512, 2), (37, 53, 64, 0), (2, 1, 64, 1),
                                             (61, 260, 1024, 2)])
-def test_whole_step(nx, ny, S, points, dtype, fuse):
+def test_whole_step(nx, ny, S, points, dtype, fuse, opts):
     """Edge flux, boundary flux and update as one loop against the separate
     loops from the same state: two steps, the first with residuals that hold
     something.  Bars: binary64 1e-12; binary32 q and adt 4 ulp of 6e-8."""
@@ -147,8 +151,7 @@ def test_whole_step(nx, ny, S, points, dtype, fuse):
     for whole in (True, False):
         t = TimeStep2D(m.x, m.q, m.e2n, m.e2c, m.b2n, m.b2c, m.c2n, QINF, device=0, block_size=S,
                        point_reorder=points, dtype=dtype)
-        t.build_plans(flux_block_size=S, schedule="dataflow", gather="lds_dma",
-                      elems_per_thread=2, fuse_adt=fuse)
+        t.build_plans(flux_block_size=S, fuse_adt=fuse, **opts)
         assert t._whole is not None
         if not whole:
             t._whole = None

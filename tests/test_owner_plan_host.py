@@ -72,6 +72,9 @@ def test_owned_cells_and_their_sides(nx, ny, order, S, layout, explicit, points)
         assert e.status == U.UM_ERR_STATE and order == "none"
         return
     assert len(got) == len(want) and dict(got) == {c: sorted(s) for c, s in want.items()}
+    # a plan of colour launches owns the same cells
+    q = L.plan("hier", S, explicit_lists=explicit)
+    assert q.stats["n_launches"] == 1 and decode(L, q) == got
     L.close()
 
 
@@ -88,13 +91,15 @@ def test_edge_between_a_cell_and_itself():
 
 
 def test_plans_without_an_owner_kernel():
-    """The register gather on AoS data and cells with more than eight sides
-    keep the waiting kernels."""
+    """The register gather of a dataflow plan on AoS data, staging of the
+    increments only and cells with more than eight sides keep their kernels."""
     m = quad_mesh(30, 20, seed=1)
     L = EdgeFluxLoop(m.x, m.q, m.adt, m.e2n, m.e2c, device=-1)
-    for kw in (dict(schedule="dataflow"), dict()):
+    for kw in (dict(schedule="dataflow"), dict(staging="inc"), dict(lds_limit_bytes=8192)):
+        p = L.plan("hier", 512, **kw)
         with pytest.raises(U.UmeshError):
-            L.export(L.plan("hier", 512, **kw), U.UM_EXP_OWNER_RECORDS)
+            L.export(p, U.UM_EXP_OWNER_RECORDS)
+        assert p.stats["n_launches"] == (1 if "schedule" in kw else p.stats["n_block_colours"])
     L.close()
     for arms, owned in ((8, True), (9, False)):
         # a star: one cell with `arms` neighbours
