@@ -188,6 +188,26 @@ __device__ __forceinline__ double block_sum(double v) {
     return t;
 }
 
+// Lane t's share of a sum of non-negative terms: terms t, t + T, t + 2T, ...
+// of T lanes, added in that order; the loads of U terms are issued before their
+// additions (a zero past the end leaves the sum unchanged).
+template <int U>
+__device__ __forceinline__ double lane_sum(const double *__restrict__ v, int32_t n) {
+    const int32_t T = int32_t(blockDim.x);
+    double acc = 0.0;
+    for (int32_t i0 = threadIdx.x; i0 < n; i0 += U * T) {
+        double u[U];
+#pragma unroll
+        for (int j = 0; j < U; ++j) {
+            const int32_t i = i0 + j * T;
+            u[j] = i < n ? v[i] : 0.0;
+        }
+#pragma unroll
+        for (int j = 0; j < U; ++j) acc += u[j];
+    }
+    return acc;
+}
+
 // The time-step scalar of a cell side by side, its sides in order: velocity and
 // sound speed of its state, then what one side adds, with the contractions
 // that the compiler gives cell_adt written out.

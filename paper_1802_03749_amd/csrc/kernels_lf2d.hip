@@ -1260,17 +1260,17 @@ __global__ __launch_bounds__(256) void finish_kernel(const int32_t *__restrict__
                                                      const double *__restrict__ partials,
                                                      int32_t n_partials, double *__restrict__ gbl) {
     if (blockIdx.x == 0) {
-        double acc = 0.0;
-        for (int32_t i = threadIdx.x; i < n_partials; i += 256) acc += partials[i];
-        const double t = dev::block_sum(acc);
-        if (threadIdx.x == 0) gbl[0] += t;
+        const double before = gbl[0];
+        const double t = dev::block_sum(dev::lane_sum<16>(partials, n_partials));
+        if (threadIdx.x == 0) gbl[0] = before + t;
         return;
     }
     constexpr int P = sizeof(Real) / 4;  // pieces per cell
     const int64_t i = int64_t(blockIdx.x - 1) * 256 + threadIdx.x;
     if (i >= int64_t(P) * n_shared) return;
     const int64_t c = shared[i / P];
-    reinterpret_cast<u32x4 *>(q)[c * P + i % P] = reinterpret_cast<const u32x4 *>(new_q)[i];
+    __builtin_nontemporal_store(reinterpret_cast<const u32x4 *>(new_q)[i],
+                                reinterpret_cast<u32x4 *>(q) + (c * P + i % P));
     if (new_adt && i % P == 0) adt[c] = new_adt[i / P];
 }
 
