@@ -242,12 +242,12 @@ typedef enum { UM_GATHER_REGISTERS = 0, UM_GATHER_LDS_DMA = 1 } um_gather;
  * same way).  A time step then reads: edge flux, boundary flux, update +
  * adt, with adt computed once before the first step.  Two launches.
  *
- * UM_K_STEP_2D -- the rest of a time step after UM_K_CELL_ADT_2D as one loop
- * over the cells: edge flux, boundary flux and update, optionally with the
- * next step's adt.  Args:
+ * UM_K_STEP_2D -- a time step as one loop over the cells: adt, edge flux,
+ * boundary flux and update, or the last three and the next step's adt.  Args:
  *   0: q   dim 4 direct, UM_RW
  *   1: res dim 4 direct, UM_RW
- *   2: adt dim 1 direct, UM_READ (kept) or UM_RW (then the new state's)
+ *   2: adt dim 1 direct, UM_WRITE (evaluated from q first) or UM_RW (read,
+ *      then the new state's)
  *   3: rms dim 1 global, UM_INC
  *   4: x   via the cell->node map (arity 4), UM_READ
  *   5: x   via the edge->node map (arity 2), UM_READ

@@ -352,7 +352,7 @@ LaunchArgs launch_args_step(Plan &p, const double *params, int32_t nparams, void
     la.n_shared = int32_t(p.hp.owner.shared.size());
     la.new_q = p.dp.new_q;
     la.new_adt = p.dp.new_adt;
-    la.keeps_adt = !sa.new_adt;
+    la.adt_mode = sa.own_adt ? STEP_OWN_ADT : STEP_NEW_ADT;
     la.own_rec = p.dp.own_rec;
     la.own_ids = p.dp.own_ids;
     la.own_words = p.dp.own_words;
@@ -751,7 +751,7 @@ um_status um_plan_build(um_ctx ctx, int32_t kernel, const um_arg *args, int32_t 
                     const int64_t w = p->sa.dtype == UM_F64 ? 8 : 4;
                     const int64_t n = int64_t(p->hp.owner.shared.size());
                     p->dp.new_q = device_alloc(4 * w * n, bytes);
-                    if (p->sa.new_adt) p->dp.new_adt = device_alloc(w * n, bytes);
+                    if (!p->sa.own_adt) p->dp.new_adt = device_alloc(w * n, bytes);
                 }
                 p->dp.bytes = bytes;
                 UM_HIP(hipDeviceSynchronize());

@@ -108,7 +108,7 @@ struct StepArgs {
     int32_t layout = UM_AOS;
     int32_t dtype = UM_F64;                      // of x, q and adt
     int32_t map_c2n = -1, map_e2n = -1, map_e2c = -1;  // UM_K_STEP_2D; boundary maps as above
-    bool new_adt = false;                        // UM_K_STEP_2D: adt is rewritten
+    bool own_adt = false;                        // UM_K_STEP_2D: adt is the old state's, written
 };
 
 // Per-block layout of a hierarchical plan, in launch order.
@@ -185,6 +185,9 @@ static_assert(sizeof(OwnRec) == 48, "OwnRec is 12 words");
 // corner, the place of the element in the corner's node's sum (owned nodes
 // only, whose staged positions come first); counts holds how many places an
 // owned node's sum has.
+// Steps that evaluate the old state's time-step scalar need the corners of the
+// staged cells that the block does not own too: they follow a block's ids, two
+// words per cell, as words 1 and 2 of the ring form (their neighbours' bits zero).
 constexpr int32_t MAX_NODE_ELEMENTS = 16;
 constexpr uint32_t NO_SIDE = 0xFFFFFFFFu, NO_CELL = 0x3FFu;
 constexpr int32_t MAX_OWNER_POINTS = 1022;     // staged cells, and staged nodes

@@ -968,9 +968,8 @@ __device__ __forceinline__ void store4_once(double *__restrict__ a, int64_t n, i
 // With STEP the residual goes on (step_kernel below): boundary sides have the
 // far field, staged behind the cells, for a neighbour, with the cell's own
 // time-step scalar; then the cell is updated and, with STEP_NEW_ADT, its next
-// time-step scalar evaluated.
-enum { FLUX_ONLY = 0, STEP_KEEP_ADT = 1, STEP_NEW_ADT = 2 };
-
+// time-step scalar evaluated.  With STEP_OWN_ADT the scalar is not staged but
+// evaluated first.
 template <typename Real>
 struct StepOut {
     Real *q, *adt;          // the state, updated in place where no other block reads it
@@ -1028,15 +1027,22 @@ __device__ __forceinline__ void owner_block(const OwnRec *__restrict__ recs,
         w = sides_of(0);
         load4<LAYOUT>(d.res, d.C, own_id, r);
     }
+    if constexpr (STEP == STEP_OWN_ADT)
+        if (tid >= n_own && tid < nc) {
+            w.y = uint32_t(my_ids[n_items + 2 * (tid - n_own)]);
+            w.z = uint32_t(my_ids[n_items + 2 * (tid - n_own) + 1]);
+        }
     auto cell_in = [&](int t0, int32_t g) {
         if constexpr (DMA && F64) {
             dma<16>(rq, q_a + 2 * t0, 32 * g);
             dma<16>(rq, q_b + 2 * t0, 32 * g + 16);
-            dma<4>(ra, adt_w + t0, 8 * g);
-            dma<4>(ra, adt_w + ns + t0, 8 * g + 4);
+            if constexpr (STEP != STEP_OWN_ADT) {
+                dma<4>(ra, adt_w + t0, 8 * g);
+                dma<4>(ra, adt_w + ns + t0, 8 * g + 4);
+            }
         } else if constexpr (DMA) {
             dma<16>(rq, q_a + 4 * t0, 16 * g);
-            dma<4>(ra, adt_w + t0, 4 * g);
+            if constexpr (STEP != STEP_OWN_ADT) dma<4>(ra, adt_w + t0, 4 * g);
         } else {
             const int t = t0 + lane;
             Real v[4];
@@ -1118,6 +1124,54 @@ __device__ __forceinline__ void owner_block(const OwnRec *__restrict__ recs,
             x0 = x_a[t]; x1 = x_b[t];
         }
     };
+    // one side at a time: unrolled, the loads of all sides are issued first
+    // and their registers leave room for fewer wavefronts
+    // (the first corner is read again at the end of the ring: two registers
+    // pairs less, 64 in all, room for an eighth wavefront)
+    auto walk = [&](auto &&visit) {
+        const uint32_t c0 = (w.y >> 10) & 0x3FFu;
+        uint32_t hs = w.x, next = (w.y >> 20) & 0x3FFu, rest = (w.z & 0xFFFFFu) | c0 << 20;
+        uint32_t slots = (w.x >> 30) | ((w.y >> 30) << 2);
+        Real xa0, xa1, xb0, xb1;
+        node(int(c0), xa0, xa1);
+#pragma unroll 1
+        for (int k = 0; k < 4; ++k) {
+            node(int(next), xb0, xb1);
+            visit(hs & 0x3FFu, xa0, xa1, xb0, xb1, slots & 1u);
+            xa0 = xb0; xa1 = xb1;
+            next = rest & 0x3FFu;
+            rest >>= 10;
+            hs = k == 2 ? w.y : hs >> 10;
+            slots >>= 1;
+        }
+    };
+    auto adt_of = [&](const Real q[4]) {
+        const dev::Wave<Real> wave = dev::wave_of(q, gm1);
+        Real sum = Real(0);
+        walk([&](uint32_t, Real xa0, Real xa1, Real xb0, Real xb1, bool) {
+            sum = sum + dev::adt_side(xa0, xa1, xb0, xb1, wave);
+        });
+        return sum;
+    };
+    if constexpr (STEP == STEP_OWN_ADT) {
+        // the state's own time-step scalar first, of every staged cell: a
+        // quarter more of them than cells, in place of a launch that reads
+        // the cells, their nodes and the map
+        if (tid < nc) {
+            Real q[4], none;
+            state(tid, q, none);
+            const Real sum = adt_of(q);
+            if constexpr (F64) {
+                const uint64_t b = __builtin_bit_cast(uint64_t, sum);
+                adt_w[tid] = uint32_t(b);
+                adt_w[ns + tid] = uint32_t(b >> 32);
+            } else {
+                adt_w[tid] = __builtin_bit_cast(uint32_t, sum);
+            }
+            if (tid < n_own) out.adt[own_id] = sum;
+        }
+        __syncthreads();
+    }
     double squares = 0.0;
     if (tid < n_own) {
         Real q[4], a;
@@ -1139,27 +1193,6 @@ __device__ __forceinline__ void owner_block(const OwnRec *__restrict__ recs,
 #pragma unroll
             for (int c = 0; c < 4; ++c) held = held || __builtin_bit_cast(uint64_t, r[c]) != 0;
         }
-        // one side at a time: unrolled, the loads of all sides are issued first
-        // and their registers leave room for fewer wavefronts
-        // (the first corner is read again at the end of the ring: two registers
-        // pairs less, 64 in all, room for an eighth wavefront)
-        auto walk = [&](auto &&visit) {
-            const uint32_t c0 = (w.y >> 10) & 0x3FFu;
-            uint32_t hs = w.x, next = (w.y >> 20) & 0x3FFu, rest = (w.z & 0xFFFFFu) | c0 << 20;
-            uint32_t slots = (w.x >> 30) | ((w.y >> 30) << 2);
-            Real xa0, xa1, xb0, xb1;
-            node(int(c0), xa0, xa1);
-#pragma unroll 1
-            for (int k = 0; k < 4; ++k) {
-                node(int(next), xb0, xb1);
-                visit(hs & 0x3FFu, xa0, xa1, xb0, xb1, slots & 1u);
-                xa0 = xb0; xa1 = xb1;
-                next = rest & 0x3FFu;
-                rest >>= 10;
-                hs = k == 2 ? w.y : hs >> 10;
-                slots >>= 1;
-            }
-        };
         if constexpr (RING) {
             walk([&](uint32_t h, Real xa0, Real xa1, Real xb0, Real xb1, bool second) {
                 if (h != NO_CELL) side(int(h), xa0, xa1, xb0, xb1, second);
@@ -1201,14 +1234,7 @@ __device__ __forceinline__ void owner_block(const OwnRec *__restrict__ recs,
             } else {
                 reinterpret_cast<float4 *>(new_q)[to] = make_float4(qn[0], qn[1], qn[2], qn[3]);
             }
-            if constexpr (STEP == STEP_NEW_ADT) {
-                const dev::Wave<Real> wave = dev::wave_of(qn, gm1);
-                Real sum = Real(0);
-                walk([&](uint32_t, Real xa0, Real xa1, Real xb0, Real xb1, bool) {
-                    sum = sum + dev::adt_side(xa0, xa1, xb0, xb1, wave);
-                });
-                (number ? out.new_adt : out.adt)[to] = sum;
-            }
+            if constexpr (STEP == STEP_NEW_ADT) (number ? out.new_adt : out.adt)[to] = adt_of(qn);
         }
     }
     if constexpr (STEP != FLUX_ONLY) {
@@ -1228,17 +1254,21 @@ __global__ __launch_bounds__(1024) void owner_kernel(const OwnRec *__restrict__ 
                                                      eps, {});
 }
 
-// A time step's edge flux, boundary flux and update (with NEW_ADT also the
-// next step's time-step scalar) in one pass over the cells, in place where a
-// cell's only reader is its own block, which has it staged.  Cells on the
-// borders between blocks (a quarter, at 16x16 cells) go to a buffer of the
-// plan, and finish_kernel stores them.  A step of 1200x600 cells, binary64 (the
-// separate loops, with the flux by owner_kernel -> here): 51.2 -> 37.6 us, 7
-// launches -> 2; 353x241 cells, binary32, adt by its own loop: 26.5 -> 13.1.
-// The kernel takes 32 us for 108 MB of counted traffic, 13 more than
-// owner_kernel: the update's divisions and the square roots of adt double the
-// arithmetic (8.7 instead of 4.6 million vector instructions).  Writing every
-// cell's next state to a buffer and copying it back took 41.6 us in all.
+// A time step's edge flux, boundary flux and update, with the time-step scalar
+// before (OWN_ADT) or after them (NEW_ADT), in one pass over the cells, in
+// place where a cell's only reader is its own block, which has it staged.
+// Cells on the borders between blocks (a quarter, at 16x16 cells) go to a buffer of
+// the plan, and finish_kernel stores them.  A step of 1200x600 cells, NEW_ADT,
+// binary64 (the separate loops, with the flux by owner_kernel -> here): 51.2 ->
+// 33.7 us, 7 launches -> 2; 353x241 cells, OWN_ADT, binary32: 26.5 -> 10.1;
+// 500x400, binary64: 52.4 (with colour launches) -> 16.8.  OWN_ADT evaluates the
+// scalar of the staged cells, a quarter more than there are; with its own
+// launch instead the last two took 12.9 and 18.9 us.  At 1200x600 the kernel
+// takes 31 us for 108 MB of counted traffic, 12 more than owner_kernel; the update's
+// divisions and the square roots of adt double the arithmetic (8.7 instead of
+// 4.6 million vector instructions), but without them it takes 29, so most of it
+// is traffic and its latency.  Writing every cell's next state to a buffer and
+// copying it back took 41.6 us in all.
 template <int STEP, bool DISS, typename Real>
 __global__ __launch_bounds__(1024) void step_kernel(const OwnRec *__restrict__ recs,
                                                     const int32_t *__restrict__ ids,
@@ -1498,6 +1528,12 @@ hipError_t lf2d_launch_one(const LaunchArgs &la, int which, int32_t begin, int32
 
 namespace {
 
+template <bool DISS, typename Real>
+auto step_form(int32_t adt_mode) {
+    return adt_mode == STEP_OWN_ADT ? step_kernel<STEP_OWN_ADT, DISS, Real>
+                                    : step_kernel<STEP_NEW_ADT, DISS, Real>;
+}
+
 template <typename Real>
 hipError_t step2d_typed(const LaunchArgs &la, int which, int32_t begin, int32_t end, int64_t lds) {
     Real *q = const_cast<Real *>(static_cast<const Real *>(la.q));
@@ -1509,12 +1545,10 @@ hipError_t step2d_typed(const LaunchArgs &la, int which, int32_t begin, int32_t 
         const StepOut<Real> out{q, adt, static_cast<Real *>(la.new_q),
                                 static_cast<Real *>(la.new_adt), la.partials,
                                 {la.qinf[0], la.qinf[1], la.qinf[2], la.qinf[3]}};
-        auto kern = la.keeps_adt ? step_kernel<STEP_KEEP_ADT, false, Real>
-                                 : step_kernel<STEP_NEW_ADT, false, Real>;
-        if constexpr (sizeof(Real) == 4)  // as in launch_owner
-            if (la.schedule == UM_SCHED_COLOUR_LAUNCHES)
-                kern = la.keeps_adt ? step_kernel<STEP_KEEP_ADT, true, Real>
-                                    : step_kernel<STEP_NEW_ADT, true, Real>;
+        // binary32: as in launch_owner
+        const bool diss = sizeof(Real) == 4 && la.schedule == UM_SCHED_COLOUR_LAUNCHES;
+        auto kern = diss ? step_form<sizeof(Real) == 4, Real>(la.adt_mode)
+                         : step_form<false, Real>(la.adt_mode);
         const hipError_t ea = allow_lds(reinterpret_cast<const void *>(kern), lds);
         if (ea != hipSuccess) return ea;
         hipLaunchKernelGGL(kern, dim3(end - begin), dim3(la.own_threads), size_t(lds), la.stream,

@@ -14,6 +14,11 @@ namespace um {
 enum { LAUNCH_HIER = 0, LAUNCH_GCOL = 1, LAUNCH_ATOMIC = 2, LAUNCH_DEBUG = 3,
        LAUNCH_HIER_FLOW = 4, LAUNCH_DIRECT = 5, LAUNCH_REDUCE = 6, LAUNCH_OWNER = 7 };
 
+// How the step kernel comes by adt: the old state's, which it evaluates and
+// stores, or that of the call before, storing the new state's (FLUX_ONLY: no
+// step, the edge loop alone).
+enum { FLUX_ONLY = 0, STEP_OWN_ADT = 1, STEP_NEW_ADT = 2 };
+
 struct LaunchArgs {
     hipStream_t stream;
     int32_t layout, staging, tcmode, block_size, ept, dtype;
@@ -46,7 +51,7 @@ struct LaunchArgs {
     const int32_t *shared; // STEP: cells that several blocks stage,
     void *new_q, *new_adt; //  their next state, until it is stored
     int32_t n_shared;
-    int32_t keeps_adt;     // STEP: 1 if adt is not rewritten
+    int32_t adt_mode;      // STEP: STEP_OWN_ADT or STEP_NEW_ADT
     int32_t n_partials;
 };
 

@@ -350,7 +350,7 @@ void build_owner_plan(const Ctx &ctx, const EdgeArgs &ea, const um_plan_opts &o,
                         }
                 }
             if (sa)
-                for (int32_t i = 0; i < 4 * r.n_own; ++i) {
+                for (int32_t i = 0; i < 4 * (sa->own_adt ? int32_t(cells.size()) : r.n_own); ++i) {
                     const int32_t n = rows_c2n[4 * int64_t(cells[i / 4]) + i % 4];
                     if (!npos[n]) {
                         npos[n] = 1;
@@ -411,6 +411,13 @@ void build_owner_plan(const Ctx &ctx, const EdgeArgs &ea, const um_plan_opts &o,
             r.node_item = int32_t(it.size());
             it.insert(it.end(), nodes.begin() + r.n_run, nodes.end());
             r.n_items = int32_t(it.size());
+            if (sa && sa->own_adt)
+                for (int32_t i = r.n_own; i < r.nc; ++i) {
+                    for (int j = 0; j < 4; ++j)
+                        corner[j] = npos[rows_c2n[4 * int64_t(cells[i]) + j]] - 1u;
+                    it.push_back(int32_t(corner[0] << 10 | corner[1] << 20));
+                    it.push_back(int32_t(corner[2] | corner[3] << 10));
+                }
             for (int32_t c : cells) cpos[c] = 0;
             for (int32_t n : nodes) npos[n] = 0;
         }
@@ -424,8 +431,11 @@ void build_owner_plan(const Ctx &ctx, const EdgeArgs &ea, const um_plan_opts &o,
         res = in_ranges(nb, E, [&](int32_t b0, int32_t b1) { return plan_range(b0, b1, ring); });
         if (res != NO_RING) break;
     }
-    for (const OwnRec &r : op.rec) {
-        op.id_stride = std::max(op.id_stride, r.n_items);
+    int32_t lanes = op.n_own_max;  // a lane per owned cell, or per cell whose adt it evaluates
+    for (int32_t k = 0; k < nb; ++k) {
+        const OwnRec &r = op.rec[k];
+        op.id_stride = std::max(op.id_stride, int32_t(items[k].size()));
+        if (sa && sa->own_adt) lanes = std::max(lanes, r.nc);
         op.lds = std::max(op.lds, owner_lds_bytes(ea.dtype, r.nc + (sa ? 1 : 0), r.nn));
     }
     if (res != OK || op.lds > (o.lds_limit_bytes > 0 ? o.lds_limit_bytes : ctx.lds_limit)) {
@@ -438,7 +448,7 @@ void build_owner_plan(const Ctx &ctx, const EdgeArgs &ea, const um_plan_opts &o,
         op.rec[k].own_off = int32_t(op.shared.size());
         op.shared.insert(op.shared.end(), shared[k].begin(), shared[k].end());
     }
-    op.threads = std::max(64, (op.n_own_max + 63) / 64 * 64);  // a lane per owned cell
+    op.threads = std::max(64, (lanes + 63) / 64 * 64);
     op.use = true;
 }
 

@@ -140,10 +140,10 @@ StepArgs check_step_args(const Ctx &ctx, int32_t kernel, const um_arg *args, int
         check_layouts(ctx, {sa.dat_x, sa.dat_q, sa.dat_res, sa.dat_adt}, "update + adt");
         sa.dtype = check_real(ctx, {sa.dat_x, sa.dat_q, sa.dat_adt}, "update + adt");
     } else if (kernel == UM_K_STEP_2D) {
-        const bool keep = nargs == 9 && args && args[2].acc == UM_READ;
+        const bool own = nargs == 9 && args && args[2].acc == UM_WRITE;
         const Want w[5] = {{4, 0, 0, UM_RW, "q", true},
                            {4, 0, 0, UM_RW, "res", false},
-                           {1, 0, 0, keep ? UM_READ : UM_RW, "adt", true},
+                           {1, 0, 0, own ? UM_WRITE : UM_RW, "adt", true},
                            {1, UM_GLOBAL, 0, UM_INC, "rms", false},
                            {2, 4, UM_ALL_SLOTS, UM_READ, "x", true}};
         if (nargs != 9 || !args) fail(UM_ERR_ARITY, "step kernel takes 9 args, got %d", nargs);
@@ -154,7 +154,7 @@ StepArgs check_step_args(const Ctx &ctx, int32_t kernel, const um_arg *args, int
         sa.dat_rms = args[3].dat;
         sa.dat_x = args[4].dat;
         sa.map_c2n = args[4].map;
-        sa.new_adt = !keep;
+        sa.own_adt = own;
         const int32_t dat[4] = {sa.dat_x, sa.dat_q, sa.dat_x, sa.dat_q}, arity[4] = {2, 2, 2, 1};
         for (int i = 5; i < 9; ++i) {
             const um_arg &a = args[i];

@@ -230,8 +230,8 @@ class TimeStep2D:
         return {k: p.stats for k, p in self.plans.items()}
 
     def _build_whole(self, flux_opts) -> None:
-        """The step's loops after adt as one loop, where the library has it
-        for the flux plan's options and this mesh."""
+        """The step's loops (with fused plans, those after adt) as one loop,
+        where the library has it for the flux plan's options and this mesh."""
         if self._whole is not None:
             U.um_plan_destroy(self._whole.handle)
             self._whole = None
@@ -241,7 +241,7 @@ class TimeStep2D:
             return
         a = U.um_arg
         args = [a(self.d_q, -1, 0, U.UM_RW), a(self.d_res, -1, 0, U.UM_RW),
-                a(self.d_adt, -1, 0, U.UM_RW if self.fused else U.UM_READ),
+                a(self.d_adt, -1, 0, U.UM_RW if self.fused else U.UM_WRITE),
                 a(self.d_rms, U.UM_GLOBAL, 0, U.UM_INC),
                 a(self.d_x, self.m_c2n, U.UM_ALL_SLOTS, U.UM_READ),
                 a(self.d_x, self.m_e2n, U.UM_ALL_SLOTS, U.UM_READ),
@@ -305,9 +305,10 @@ class TimeStep2D:
         fused plans the adt of a step comes from the previous step's update
         (computed here only before the first step, or after invalidate_adt).
         With a flux plan of colour launches, or a dataflow one that gathers by
-        LDS DMA, the loops after adt run as one (UM_K_STEP_2D) where the mesh
-        allows it; the results are those of the separate loops, to rounding."""
-        if not self.fused or not self.adt_valid:
+        LDS DMA, the step is one loop (UM_K_STEP_2D; with fused plans all but a
+        first adt) where the mesh allows it; the results are those of the
+        separate loops, to rounding."""
+        if not self.adt_valid and (self.fused or self._whole is None):
             self.run_loop("adt", stream)
         if self._whole is not None:
             U.um_loop_exec(self._whole.handle, self.params("bres"),
@@ -324,8 +325,8 @@ class TimeStep2D:
             n = self._whole.stats["n_launches"]
         else:
             n = sum(self.plans[k].stats["n_launches"]
-                    for k in ("flux", "bres", "upa" if self.fused else "upd"))
-        return n + (0 if self.fused else self.plans["adt"].stats["n_launches"])
+                    for k in ("flux", "bres") + (("upa",) if self.fused else ("upd", "adt")))
+        return n
 
     def close(self) -> None:
         if self.ctx:

@@ -162,20 +162,23 @@ def test_hex_owned_nodes_and_their_elements(n, S, explicit, points):
     L.close()
 
 
-def step(m, **kw):
+def step(m, fuse=False, **kw):
     T = TimeStep2D(m.x, m.q, m.e2n, m.e2c, m.b2n, m.b2c, m.c2n, [1.0, 0.35, 0.05, 2.7],
                    device=-1, block_size=64, **kw)
-    T.build_plans(flux_block_size=64, schedule="dataflow", gather="lds_dma", elems_per_thread=2)
+    T.build_plans(flux_block_size=64, schedule="dataflow", gather="lds_dma", elems_per_thread=2,
+                  fuse_adt=fuse)
     return T
 
 
+@pytest.mark.parametrize("fuse", [False, True])
 @pytest.mark.parametrize("points", [0, 2])
 @pytest.mark.parametrize("nx,ny", [(23, 17), (2, 1), (5, 1)])
-def test_step_plan_has_every_side_of_every_cell(nx, ny, points):
+def test_step_plan_has_every_side_of_every_cell(nx, ny, points, fuse):
     """The step's plan owns every cell; side k of a cell runs from node k to
-    node k + 1 of its row and has the edge or boundary edge that lies there."""
+    node k + 1 of its row and has the edge or boundary edge that lies there.
+    Steps that evaluate adt first have the corners of the other staged cells."""
     m = quad_mesh(nx, ny, seed=8)
-    T = step(m, point_reorder=points)
+    T = step(m, fuse, point_reorder=points)
     h = T._whole.handle
     get = lambda f: (lambda out: (U.um_plan_export(h, f, out, out.size), out)[1])(
         np.empty(U.um_plan_export(h, f), np.int32))
@@ -205,8 +208,12 @@ def test_step_plan_has_every_side_of_every_cell(nx, ny, points):
                 assert (nodes[a], nodes[b]) == (c2n[c, k], c2n[c, (k + 1) % 4])
                 assert ((int(cells[h]) if h >= 0 else int(h)), int(slot)) == want
         row += n_own
+        for i in range(n_own, 0 if fuse else nc):
+            lo, hi = it[n_items + 2 * (i - n_own):][:2]
+            corners = [(lo >> 10) & 1023, (lo >> 20) & 1023, hi & 1023, (hi >> 10) & 1023]
+            assert nodes[corners].tolist() == c2n[cells[i]].tolist()
     assert sorted(seen) == list(range(T.C))
-    assert T.step_launches() == 3
+    assert T.step_launches() == 2
     T.close()
 
 
@@ -217,7 +224,7 @@ def test_step_plan_refused():
     m = quad_mesh(6, 5, seed=8)
     m.b2n[3] = m.b2n[3, ::-1]
     T = step(m)
-    assert T._whole is None and T.step_launches() > 3
+    assert T._whole is None and T.step_launches() > 2
     T.close()
     m = quad_mesh(6, 5, seed=8)
     m.b2n, m.b2c = np.concatenate([m.b2n, m.b2n[:1]]), np.concatenate([m.b2c, m.b2c[:1]])
