@@ -201,7 +201,8 @@ def step_gaps(outdir: str, per_step: int, n_steps: int, skip_steps: int = 2):
                              _kernel_key(r["Kernel_Name"])))
     rows.sort()
     names = [r[2] for r in rows]
-    fpat = r"hier_dma_kernel|hier_flow_kernel|hier_kernel|gcol_kernel|atomic_kernel"
+    fpat = r"owner_kernel|step_kernel|hier_dma_kernel|hier_flow_kernel|hier_kernel|gcol_kernel|" \
+        r"atomic_kernel"
     flux = [i for i, k in enumerate(names) if re.search(fpat, k)]
     # a step may hold several flux launches (colour launches): a step opens
     # with a flux launch that follows a dispatch of another kernel; the
@@ -270,8 +271,8 @@ def driver(args, passthrough) -> int:
     kib = 1024.0
     fetch_scale = COPY_BYTES / kib / copy_f
     write_scale = COPY_BYTES / kib / copy_w
-    kpat = r"hier_dma_kernel|hier_flow_kernel|hier_kernel" if args.loop == "edge" \
-        else r"hex_flow_kernel|hex_hier_kernel"
+    kpat = r"(?<!hex_)owner_kernel|hier_dma_kernel|hier_flow_kernel|hier_kernel" \
+        if args.loop == "edge" else r"hex_owner_kernel|hex_flow_kernel|hex_hier_kernel"
     lf, nl = _mean_of(fetch, kpat)
     lw, _ = _mean_of(write, kpat)
     kname = sorted(k for k in fetch if re.search(kpat, k))

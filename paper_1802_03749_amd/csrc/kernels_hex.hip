@@ -12,6 +12,10 @@
 //                    read-modify-write of force.
 //  hex_flow_kernel   the dataflow schedule: one launch, each block waits for
 //                    its earlier-coloured neighbours before its write-back.
+//  hex_owner_kernel  hierarchical plans wherever the planner gives them an
+//                    owner plan: every node is incremented by one of its
+//                    blocks, which evaluates the elements on its border too;
+//                    one launch, no order between blocks.
 //  hex_atomic_kernel one launch, hardware FP64 atomic adds.
 //  hex_debug_kernel  per-element forces with contraction disabled.
 #include <hip/hip_runtime.h>
@@ -389,10 +393,10 @@ __device__ __forceinline__ void hex_component(const double v[8], double c, doubl
 // At 96^3 the gather alone takes 26 us (132 MB counted, the memory's rate),
 // the evaluation alone 28 (LDS busy for 16 us, the vector units for 13), the
 // sweep 34.5; the waiting kernel 49.9.  At 33^3 (SoA), where a chain of eight
-// colours was everything, 28.3 -> 6.9 us.  Taking three blocks to a compute
-// unit instead of four costs 2 %; staging the nodes in the elements' order, or
-// the largest blocks' sums in several passes to fit a fourth block, gained
-// nothing.
+// colours was everything, 28.3 -> 6.9 us; with a launch per colour 96^3 took
+// 117.1 us.  Taking three blocks to a compute unit instead of four costs 2 %;
+// staging the nodes in the elements' order, or the largest blocks' sums in
+// several passes to fit a fourth block, gained nothing.
 template <int LAYOUT>
 __global__ __launch_bounds__(1024) void hex_owner_kernel(
     const OwnRec *__restrict__ recs, const int32_t *__restrict__ ids, int32_t id_stride,

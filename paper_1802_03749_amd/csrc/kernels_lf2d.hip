@@ -13,7 +13,13 @@
 //  hier_flow_kernel  the same per-block work as one launch over all blocks
 //                in colour order (dataflow schedule): a block's residual
 //                read-modify-write waits for its earlier-coloured neighbours'
-//                completion flags instead of a kernel boundary.
+//                completion flags instead of a kernel boundary;
+//                hier_dma_kernel is its form with the LDS-DMA gather.
+//  owner_kernel  hierarchical plans wherever the planner gives them an owner
+//                plan: every cell is incremented by one of its blocks, which
+//                evaluates the edges on its border too; one launch, no order
+//                between blocks.
+//  step_kernel, finish_kernel  a whole time step on owner plans (UM_K_STEP_2D).
 //  gcol_kernel   global colouring baseline (Section 2.1): one launch per
 //                colour, gather through the int32 maps, plain read-modify-
 //                write of res.
@@ -948,7 +954,7 @@ __device__ __forceinline__ void store4_once(double *__restrict__ a, int64_t n, i
     }
 }
 
-// Owner kernel: the dataflow schedule's blocks without an order between them
+// Owner kernel: a hierarchical plan's blocks without an order between them
 // (planner_owner.cpp).  A block stages the cells and nodes around the cells it
 // owns, and lane i adds the outgoing fluxes of owned cell i to its residual in
 // registers, in a fixed order, and stores it.  Every edge is evaluated from
@@ -963,8 +969,9 @@ __device__ __forceinline__ void store4_once(double *__restrict__ a, int64_t n, i
 // sweep, three meshes in turn (waiting kernels -> here): binary64 200x100
 // cells 14.8 -> 4.9 us (what submitting a launch takes), 1200x600 31.6 -> 19.4,
 // 2400x1200 80.9 -> 72.4 (5.8 TB/s of counted traffic), binary32 1133x711 29.5
-// -> 15.9, SoA (staged through registers) 907x613 28.7 -> 15.1.  Blocks that
-// are chunks of the RCM order stage 1.5 times the cells: 33.5 -> 28.6.
+// -> 15.9, SoA (staged through registers) 907x613 28.7 -> 15.1; instead of five
+// colour launches, 600x300 29.8 -> 7.9.  Blocks that are chunks of the RCM order
+// stage 1.5 times the cells: 33.5 -> 28.6.
 // With STEP the residual goes on (step_kernel below): boundary sides have the
 // far field, staged behind the cells, for a neighbour, with the cell's own
 // time-step scalar; then the cell is updated and, with STEP_NEW_ADT, its next

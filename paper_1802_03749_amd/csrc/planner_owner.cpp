@@ -1,4 +1,4 @@
-// Host plans of the owner kernels: the dataflow schedule's blocks without an
+// Host plans of the owner kernels: a hierarchical plan's blocks without an
 // order between them.  Every point that a loop increments belongs to one of
 // the blocks that touch it, and that block evaluates every element around
 // the point; elements on a border between blocks are evaluated by each

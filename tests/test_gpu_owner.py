@@ -1,4 +1,4 @@
-"""GPU parity of the owner kernels (dataflow plans without waits) against the
+"""GPU parity of the owner kernels (blocks without an order) against the
 CPU oracle, at the forms their plans take.  Edge loop: cells whose sides close
 a ring and cells of any other shape with up to eight sides, runs and listed
 ids, both layouts and storage types, one and many wavefronts per block.  Hex
