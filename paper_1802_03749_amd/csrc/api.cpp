@@ -317,6 +317,12 @@ bool is_step_kernel(int32_t k) {
            k == UM_K_UPDATE_ADT_2D || k == UM_K_STEP_2D;
 }
 
+// As the edge flux loop that the step kernel runs in place of.
+void check_step_overlap(const Ctx &c, const StepArgs &sa) {
+    const int32_t reads[3] = {sa.dat_x, sa.dat_q, sa.dat_adt};
+    check_no_overlap(c, sa.dat_res, reads, 3, "step kernel");
+}
+
 LaunchArgs launch_args_step(Plan &p, const double *params, int32_t nparams, void *stream) {
     const Ctx &ctx = *p.ctx;
     if (ctx.device < 0) fail(UM_ERR_STATE, "host-only context cannot execute");
@@ -337,6 +343,7 @@ LaunchArgs launch_args_step(Plan &p, const double *params, int32_t nparams, void
     if (ctx.sets[p.iter_set].size > 0)
         for (int id : ids)
             if (id >= 0 && !ctx.dats[id].ptr) fail(UM_ERR_STATE, "a dat of the loop has no device memory");
+    if (p.kernel == UM_K_STEP_2D) check_step_overlap(ctx, sa);
     if (sa.dat_x >= 0) {
         la.x = ctx.dats[sa.dat_x].ptr;
         la.N = ctx.sets[ctx.dats[sa.dat_x].set].size;
@@ -706,6 +713,7 @@ um_status um_plan_build(um_ctx ctx, int32_t kernel, const um_arg *args, int32_t 
                 if (o.gather != UM_GATHER_REGISTERS && kernel != UM_K_STEP_2D)
                     fail(UM_ERR_UNSUPPORTED, "LDS-DMA gather: edge flux loop only");
                 p->sa = check_step_args(c, kernel, args, nargs, iter_set);
+                if (kernel == UM_K_STEP_2D) check_step_overlap(c, p->sa);
                 build_host_plan_step(c, kernel, p->sa, iter_set, o, p->hp);
             } else {
                 if (o.gather != UM_GATHER_REGISTERS)

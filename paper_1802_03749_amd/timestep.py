@@ -252,7 +252,7 @@ class TimeStep2D:
         try:
             h = U.um_plan_build(self.ctx, U.UM_K_STEP_2D, args, self.s_cells, o)
         except U.UmeshError as e:
-            if e.status != U.UM_ERR_UNSUPPORTED:
+            if e.status not in (U.UM_ERR_UNSUPPORTED, U.UM_ERR_NOMEM):
                 raise
             return
         self._whole = Plan(h, "hier", o.block_size, U.um_plan_stats_get(h).as_dict())

@@ -171,6 +171,19 @@ def test_whole_step(nx, ny, S, points, dtype, fuse, opts):
         t.close()
 
 
+def test_whole_step_refuses_overlapping_dats():
+    """res re-pointed into q is refused at the step, as by the edge flux loop."""
+    m = quad_mesh(20, 10, seed=3)
+    t = TimeStep2D(m.x, m.q, m.e2n, m.e2c, m.b2n, m.b2c, m.c2n, QINF, device=0, block_size=64)
+    t.build_plans(flux_block_size=64)
+    assert t._whole is not None
+    U.um_set_dat_ptr(t.ctx, t.d_res, t.q.data_ptr())
+    with pytest.raises(U.UmeshError) as ei:
+        t.step()
+    assert ei.value.status == U.UM_ERR_ARG
+    t.close()
+
+
 def test_whole_step_in_a_graph():
     """Replays of a captured step against eager steps."""
     m = quad_mesh(200, 90, seed=12)
