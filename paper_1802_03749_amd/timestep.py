@@ -300,6 +300,9 @@ class TimeStep2D:
         plans the next step then starts with the adt loop again."""
         self.adt_valid = False
 
+    def _runs_whole(self) -> bool:
+        return self._whole is not None and not U.any_timed(self.plans.values())
+
     def step(self, stream=None) -> None:
         """Enqueue one time step: adt, edge flux, boundary flux, update; with
         fused plans the adt of a step comes from the previous step's update
@@ -307,10 +310,12 @@ class TimeStep2D:
         With a flux plan of colour launches, or a dataflow one that gathers by
         LDS DMA, the step is one loop (UM_K_STEP_2D; with fused plans all but a
         first adt) where the mesh allows it; the results are those of the
-        separate loops, to rounding."""
-        if not self.adt_valid and (self.fused or self._whole is None):
+        separate loops, to rounding.  While one of the loops' own plans is
+        timed (um_plan_set_timing) they run separately."""
+        whole = self._runs_whole()
+        if not self.adt_valid and (self.fused or not whole):
             self.run_loop("adt", stream)
-        if self._whole is not None:
+        if whole:
             U.um_loop_exec(self._whole.handle, self.params("bres"),
                            self.stream if stream is None else stream)
         else:
@@ -321,7 +326,7 @@ class TimeStep2D:
     def step_launches(self) -> int:
         """Kernel launches of one step (with fused plans, of one whose adt is
         the previous step's)."""
-        if self._whole is not None:
+        if self._runs_whole():
             n = self._whole.stats["n_launches"]
         else:
             n = sum(self.plans[k].stats["n_launches"]

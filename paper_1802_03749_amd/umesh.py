@@ -257,6 +257,7 @@ def um_plan_build(ctx: int, kernel: int, args, iter_set: int, opts: um_plan_opts
     h = _P()
     _check(lib().um_plan_build(ctx, kernel, arr, len(args), iter_set, ct.byref(opts), ct.byref(h)),
            "um_plan_build")
+    _timed.discard(h.value)  # it may be the address of a plan that is gone
     return h.value
 
 
@@ -273,6 +274,7 @@ def um_plan_autotune(ctx: int, kernel: int, args, iter_set: int, candidates, par
                                   ct.cast(p, ct.c_void_p), len(params), stream, reps,
                                   ct.byref(best), ct.cast(ms, ct.c_void_p), ct.byref(h)),
            "um_plan_autotune")
+    _timed.discard(h.value)
     return h.value, best.value, list(ms)
 
 
@@ -302,8 +304,17 @@ def um_loop_exec_static(plan: int, params, stream: int) -> None:
     _check(lib().um_loop_exec_static(plan, p, len(params), stream), "um_loop_exec_static")
 
 
+_timed: set[int] = set()  # plans whose launches are being timed
+
+
 def um_plan_set_timing(plan: int, enable: bool) -> None:
     _check(lib().um_plan_set_timing(plan, 1 if enable else 0), "um_plan_set_timing")
+    (_timed.add if enable else _timed.discard)(plan)
+
+
+def any_timed(plans) -> bool:
+    """Whether um_plan_set_timing is on for one of these plans."""
+    return bool(_timed) and any(p.handle in _timed for p in plans)
 
 
 def um_plan_timing(plan: int):
