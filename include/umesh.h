@@ -631,7 +631,10 @@ um_status um_loop_exec_static(um_plan plan, const double *params, int32_t nparam
 
 /* Autotuning: build a plan for each of the n_candidates option sets, run
  * each once untimed and then `reps` times between two HIP events on
- * `stream`, keep the fastest plan in *out and destroy the others.  The
+ * `stream`, keep the fastest plan in *out and destroy the others (of a
+ * COLOUR_LAUNCHES and a DATAFLOW plan that are one kernel in two binary32
+ * roundings, see um_schedule, the DATAFLOW one: both then report the smaller
+ * of their times).  The
  * loop's written dats (INC, WRITE, RW) are modified by the trial runs: the
  * caller re-initialises them afterwards.  A candidate whose build fails
  * with UM_ERR_LDS, UM_ERR_COLOURS, UM_ERR_UNSUPPORTED or UM_ERR_ARG, or
