@@ -106,34 +106,41 @@ typedef enum { UM_TC_BARRIER = 0, UM_TC_LDS_ATOMIC = 1 } um_tcmode;
  * time; the plan keeps the fewest colours found.  Slower to build. */
 typedef enum { UM_BCOL_FIRST_FIT = 0, UM_BCOL_RECOLOUR = 1, UM_BCOL_MIN = 2 } um_bcolouring;
 /* How block colours are ordered in time (HIER), where an order is needed (see
- * below).  COLOUR_LAUNCHES: one kernel
- * launch per block colour (the kernel boundary orders colours, Section 2.2).
+ * below).  COLOUR_LAUNCHES: one kernel launch per block colour (the kernel
+ * boundary orders colours, Section 2.2).
  * DATAFLOW: one launch over all blocks in colour order; each block computes
  * its fluxes, then waits until every neighbouring block of an earlier colour
  * has published its write-back, then loads and updates its residuals.  The
  * schedule's residual loads and stores carry device-scope coherence (they
  * bypass the per-XCD L2 caches' stale lines), a block's completion flag is
  * stored once its residual stores have completed and polled with
- * device-scope loads.  Needs 32 * (cells) < 2^31.  The per-cell order of additions is the same as
- * with colour launches; results agree to rounding (the two kernels may pair
- * multiply-adds into FMAs differently) and each schedule is bitwise
- * reproducible from run to run.
+ * device-scope loads.  Needs 32 * (cells) < 2^31.  The per-cell order of
+ * additions is the same as with colour launches; results agree to rounding
+ * (the two kernels may pair multiply-adds into FMAs differently) and each
+ * schedule is bitwise reproducible from run to run.
  * A wait that exceeds a time limit counts an error of the plan instead of
- * hanging (um_plan_errors, um_plan_set_wait_limit).  Each block's flag counts the executions it has
- * completed (all flags advance together), so the launch needs no host-side
- * counter and may be captured in a HIP graph and replayed.  Supported for STAGE_ALL with one or two
- * elements per lane; a plan must not execute concurrently with itself.
- * Of either schedule, STAGE_ALL plans need no order between blocks where no
- * cell has more than 8 edges (no node more than 16 elements), no block stages
- * more than 1023 points of a set and q, x and force stay below 2^31 bytes:
- * they run the owner kernels, in which each point is incremented by one of
- * its blocks only, which evaluates all elements around it, those on its
- * border too.  DATAFLOW plans do so with the LDS-DMA gather or SoA data
- * (binary32: at two elements per lane), of the hex loop with at most
- * 2,000,000 elements.  Such a plan is one launch, without waits, flags and
- * colour rounds; its results are reproducible bit for bit in every um_tcmode.  The block and thread colours, the launch
- * order by colour and the statistics below describe the plan's blocks all
- * the same. */
+ * hanging (um_plan_errors, um_plan_set_wait_limit).  Each block's flag counts
+ * the executions it has completed (all flags advance together), so the launch
+ * needs no host-side counter and may be captured in a HIP graph and replayed.
+ * Supported for STAGE_ALL with one or two elements per lane; a plan must not
+ * execute concurrently with itself.
+ * Of either schedule, STAGE_ALL plans whose blocks need no order run the
+ * owner kernels: each point is incremented by one of its blocks only, its
+ * owner, which stages and evaluates all elements around its points, those on
+ * its border too.  Such a plan is one launch, without waits, flags and colour
+ * rounds; its results are reproducible bit for bit in every um_tcmode.
+ *   Edge loop: no cell has more than 8 edges, no block stages more than 1022
+ *   cells or 1022 nodes, 32 * (cells) and 16 * (nodes) are below 2^31 (in
+ *   either precision); DATAFLOW plans have the LDS-DMA gather, or SoA data
+ *   (binary32: and two elements per lane).
+ *   Hex loop: no node has more than 16 elements, no block stages more than
+ *   1022 nodes or evaluates more than 1024 elements, 24 * (nodes) is below
+ *   2^31; DATAFLOW plans have at most 2,000,000 elements.
+ *   Both: a block's staged data (hex: and sums) fit the LDS limit.
+ * All other plans keep the order of their schedule.  UM_EXP_OWNER_RECORDS is
+ * defined for owner plans only, and tells them apart.  An owner plan's block
+ * and thread colours, launch order by colour and statistics describe its
+ * blocks all the same, though its kernel has no use for them. */
 typedef enum { UM_SCHED_COLOUR_LAUNCHES = 0, UM_SCHED_DATAFLOW = 1 } um_schedule;
 /* How a DATAFLOW block of the edge loop moves its staged data from HBM to
  * LDS (Section 2.2's gather step).  REGISTERS: each lane loads a staged
@@ -257,13 +264,13 @@ typedef enum { UM_GATHER_REGISTERS = 0, UM_GATHER_LDS_DMA = 1 } um_gather;
  * (4 to 7 with idx UM_ALL_SLOTS).  params = {gm1, eps, qinf0..3}.  AoS data;
  * options as for an edge-flux plan, HIER with STAGE_ALL staging and the
  * DATAFLOW schedule with the LDS-DMA gather, or COLOUR_LAUNCHES (they differ
- * in the rounding of binary32 fluxes, as the edge-flux plans do).  Every side of a cell (from node k to node k + 1 of its
- * row) must be one edge's or boundary edge's, with the normal pointing out
- * of the edge's first cell, or nobody's, and every cell needs an edge:
- * UM_ERR_UNSUPPORTED otherwise.  Results as of the separate loops, to
- * rounding (the additions to res and rms come in another order); res is
- * read, and zero afterwards.  Two launches; the plan owns a buffer for the
- * cells on the borders between its blocks.
+ * in the rounding of binary32 fluxes, as the edge-flux plans do).  Every side
+ * of a cell (from node k to node k + 1 of its row) must be one edge's or
+ * boundary edge's, with the normal pointing out of the edge's first cell, or
+ * nobody's, and every cell needs an edge: UM_ERR_UNSUPPORTED otherwise.
+ * Results as of the separate loops, to rounding (the additions to res and rms
+ * come in another order); res is read, and zero afterwards.  Two launches; the
+ * plan owns a buffer for the cells on the borders between its blocks.
  */
 typedef enum {
     UM_K_EDGE_FLUX_LF2D = 0,
@@ -351,7 +358,10 @@ typedef struct {
                                   per block: UM_ERR_ARG when the padded slots
                                   exceed 1024 * elems_per_thread)           */
     int32_t xcd_groups;        /* HIER, edge and hex loops: 0 or 1 = blocks
-                                  launched in colour order as planned;
+                                  launched in colour order as planned (owner
+                                  plans, see um_schedule: in eight ranges, or
+                                  in windows of 256 blocks where the data
+                                  exceed the last-level cache);
                                   G = 2..64: the blocks form G equal ranges
                                   of block ids (regions of space in
                                   partition order) and inside each block

@@ -151,7 +151,7 @@ struct FlowRec {
 };
 static_assert(sizeof(FlowRec) == 256, "FlowRec is 256 bytes");
 
-// The owner kernel of the edge loop (planner_owner.cpp): per block, in
+// The owner kernels (planner_owner.cpp), here of the edge loop: per block, in
 // launch order, the cells it owns and the cells and nodes it stages.  Staged
 // cells are the owned ones, then the others; the first c_run of them are
 // consecutive ids from c_start, the rest are listed, and the nodes likewise.
@@ -177,7 +177,8 @@ static_assert(sizeof(OwnRec) == 48, "OwnRec is 12 words");
 //   h3 | c0 << 10 | c1 << 20 | slot2 << 30 | slot3 << 31,  c2 | c3 << 10
 // in three planes per block.  In the step's plan a boundary side's neighbour
 // is the position after the last staged cell, and c3's word goes on with the
-// cell's number, from 1, among the block's cells that other blocks stage too.  General form: 4 * quads words per cell, each
+// cell's number, from 1, among the block's cells that other blocks stage too.
+// General form: 4 * quads words per cell, each
 // h | a << 10 | b << 20 | slot << 30, NO_SIDE for a missing side.
 // Hex loop: nodes are owned, nc counts the staged nodes and nn the evaluated
 // elements, word_off those of the earlier blocks.  An element's four words:
@@ -237,14 +238,14 @@ struct HostPlan {
     int32_t max_tcol = 0;
     double avg_tcol = 0.0, reuse = 0.0;
     int64_t lds_max = 0, staged_total = 0;
-    OwnerPlan owner;                           // DATAFLOW edge loop without waits
+    OwnerPlan owner;                           // HIER: blocks without an order, if used
 };
 
 void build_host_plan(const Ctx &ctx, const EdgeArgs &ea, int32_t iter_set,
                      const um_plan_opts &o, HostPlan &hp);
 std::vector<int32_t> block_ranges(const Set &is, int32_t block_size, bool &own);
-// Fills hp.owner of a dataflow edge plan where its blocks allow it.  With
-// `sa`, of the whole step's: every cell must then be owned, and its sides are
+// Fills hp.owner of an edge plan (either schedule) where its blocks allow it,
+// else leaves it unused.  With `sa`, of the whole step's: every cell must then be owned, and its sides are
 // those of its cell->node row, each an edge's or a boundary edge's.
 void build_owner_plan(const Ctx &ctx, const EdgeArgs &ea, const um_plan_opts &o, HostPlan &hp,
                       const StepArgs *sa = nullptr);

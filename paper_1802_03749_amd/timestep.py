@@ -10,9 +10,10 @@ Marshalling only.  A step is four library loops, enqueued on one stream:
 With build_plans(fuse_adt=True) the update and the next step's adt run as
 one cell loop ("upa", the library's UM_K_UPDATE_ADT_2D): adt is computed
 once before the first step and each step is then flux, bres, upa, with the
-same results bit for bit and one pass over q fewer.  With a dataflow flux plan
-that gathers by LDS DMA, step() runs flux, bres and upd or upa as one loop (the
-library's UM_K_STEP_2D), equal to rounding.
+same results bit for bit and one pass over q fewer.  With a flux plan of colour
+launches (the default), or a dataflow one that gathers by LDS DMA, on AoS data,
+step() runs all of them (with fused plans, all but a first adt) as one loop, the
+library's UM_K_STEP_2D, where the mesh allows it, equal to rounding.
 
 The mesh may be one mesh or the disjoint union of many (meshgen.union): the
 loops do not care, so a batch of meshes runs as one set of launches.  The
