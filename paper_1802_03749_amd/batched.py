@@ -74,6 +74,7 @@ class BatchedSteps:
             self.steps = [ts]
         else:
             self.steps = []
+            whole = {}  # per bucket, the options of the step as one loop
             for m in self.meshes:
                 ts = TimeStep2D(m.x, m.q, m.e2n, m.e2c, m.b2n, m.b2c, m.c2n, qinf,
                                 device=device, block_size=partition_block, dtype=dtype)
@@ -83,6 +84,7 @@ class BatchedSteps:
                     ts.run_loop("adt")
                     best, ms = ts.autotune_flux(self.candidates, tune_reps)
                     self.tuned[b] = (self.candidates[best], ms)
+                    whole[b] = ts.whole_options
                 else:
                     c = self.tuned[b][0]
                     ts.build_plans(flux_block_size=c["block_size"],
@@ -93,6 +95,8 @@ class BatchedSteps:
                                    gather=c.get("gather", "registers"),
                                    wave_colour_groups=c.get("wave_colour_groups", False),
                                    fuse_adt=fuse_adt)
+                    if ts.whole_options is None and whole[b] is not None:
+                        ts._build_whole(whole[b])
                 self.steps.append(ts)
         torch.cuda.synchronize()
         # the trial runs changed nothing but res (zeroed again) and adt

@@ -94,6 +94,7 @@ class TimeStep2D:
             U.um_reorder_mesh(ctx, o)
         self.plans: dict[str, Plan] = {}
         self._whole: Plan | None = None  # edge flux, boundary flux and update as one loop
+        self.whole_options: dict | None = None  # and the flux options it was built for
         if device >= 0:
             self.dev = torch.device("cuda", device)
             self.stream = torch.cuda.current_stream(self.dev).cuda_stream
@@ -230,15 +231,21 @@ class TimeStep2D:
                                gather=gather) if flux_strategy == "hier" else {})
         return {k: p.stats for k, p in self.plans.items()}
 
+    def _may_run_whole(self, flux_opts) -> bool:
+        """Whether the library has the step as one loop for these options (the
+        register gather of a dataflow plan asks for that plan's own kernel)."""
+        o = flux_opts
+        return (bool(o) and self.layout == U.UM_AOS and o.get("staging", "all") == "all" and
+                (o.get("schedule") != "dataflow" or o.get("gather") == "lds_dma"))
+
     def _build_whole(self, flux_opts) -> None:
         """The step's loops (with fused plans, those after adt) as one loop,
         where the library has it for the flux plan's options and this mesh."""
         if self._whole is not None:
             U.um_plan_destroy(self._whole.handle)
             self._whole = None
-        # the register gather of a dataflow plan asks for that plan's own kernel
-        if not flux_opts or (flux_opts.get("schedule") == "dataflow" and
-                             flux_opts.get("gather") != "lds_dma"):
+        self.whole_options = None
+        if not self._may_run_whole(flux_opts):
             return
         a = U.um_arg
         args = [a(self.d_q, -1, 0, U.UM_RW), a(self.d_res, -1, 0, U.UM_RW),
@@ -257,6 +264,7 @@ class TimeStep2D:
                 raise
             return
         self._whole = Plan(h, "hier", o.block_size, U.um_plan_stats_get(h).as_dict())
+        self.whole_options = dict(flux_opts)
 
     def flux_args(self):
         a = U.um_arg
@@ -268,8 +276,11 @@ class TimeStep2D:
     def autotune_flux(self, candidates, reps: int = 5):
         """Let the library time the edge-flux loop under each candidate
         (dicts of block_size, schedule, staging, block_colouring, tcmode) and
-        keep the fastest as the step's flux plan.  adt must be valid (run the
-        adt loop first); res is zeroed afterwards.  Returns (index, ms list)."""
+        keep the fastest as the step's flux plan.  Where that one's options
+        rule out the step as one loop (register gather, increments only), the
+        step takes the fastest that allow it if they are as fast to 10 %: the
+        separate loops cost more than that.  adt must be valid (run the adt loop first); res is zeroed
+        afterwards.  Returns (index, ms list)."""
         opts = [self._opts("hier", **c) for c in candidates]
         h, best, ms = U.um_plan_autotune(self.ctx, U.UM_K_EDGE_FLUX_LF2D, self.flux_args(),
                                          self.s_edges, opts, self.params("flux"), self.stream,
@@ -279,7 +290,14 @@ class TimeStep2D:
             U.um_plan_destroy(old.handle)
         self.plans["flux"] = Plan(h, "hier", candidates[best]["block_size"],
                                   U.um_plan_stats_get(h).as_dict())
-        self._build_whole(candidates[best])
+        fastest = [candidates[i] for i in sorted(range(len(ms)), key=lambda i: (i != best, ms[i]))
+                   if 0 < ms[i] <= 1.1 * ms[best] and self._may_run_whole(candidates[i])]
+        self._build_whole({})
+        tried = set()
+        for c in fastest:  # the mesh may refuse a block size
+            if self._whole is None and c["block_size"] not in tried:
+                tried.add(c["block_size"])
+                self._build_whole(c)
         self.res.zero_()
         return best, ms
 

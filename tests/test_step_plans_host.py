@@ -1,5 +1,7 @@
-"""Which loop a time step runs (host-only contexts)."""
+"""Which loop a time step runs (host-only contexts): after autotuning, and
+while its loops' own plans are timed."""
 import numpy as np
+import pytest
 import torch
 
 from meshgen import quad_mesh
@@ -14,6 +16,58 @@ def make(m, **kw):
                    **kw)
     T.stream, T.res = None, torch.zeros(T.C, 4, dtype=torch.float64)
     return T
+
+
+@pytest.fixture
+def times(monkeypatch):
+    """The autotuner with given times instead of a device."""
+    given = []
+
+    def tune(ctx, kernel, args, iter_set, candidates, params, stream, reps=5):
+        best = min((i for i, t in enumerate(given) if t > 0), key=lambda i: given[i])
+        return U.um_plan_build(ctx, kernel, args, iter_set, candidates[best]), best, list(given)
+
+    monkeypatch.setattr(U, "um_plan_autotune", tune)
+    return given
+
+
+CANDIDATES = [dict(block_size=128, schedule="dataflow"), dict(block_size=128, staging="inc"),
+              dict(block_size=64), dict(block_size=128, schedule="dataflow", gather="lds_dma"),
+              dict(block_size=1024)]
+
+
+@pytest.mark.parametrize("ms,flux,whole", [
+    ([1.0, 1.2, 0.9, 1.2, 1.2], 2, 2), ([1.0, 1.0, 1.09, 1.08, 1.2], 0, 3),
+    ([1.0, 0.9, 0.97, 2.0, -1.0], 1, 2), ([1.0, 1.1, -1.0, -1.0, 1.05], 0, 4),
+    ([1.0, 1.05, -1.0, -1.0, -1.0], 0, None), ([1.0, 1.05, 1.2, 1.11, 1.2], 0, None)])
+def test_autotuned_step_stays_one_loop(times, ms, flux, whole):
+    """A candidate that the step as one loop cannot run (register gather,
+    increments only) may have the fastest edge flux; the step then takes the
+    fastest of those that can, if it is as fast to 10 %."""
+    times[:] = ms
+    T = make(quad_mesh(23, 17, seed=8))
+    T.build_plans(flux_block_size=64)
+    best, _ = T.autotune_flux(CANDIDATES)
+    assert best == flux and T.plans["flux"].block_size == CANDIDATES[flux]["block_size"]
+    assert T.whole_options == (None if whole is None else CANDIDATES[whole])
+    assert (T.step_launches() == 2) == (whole is not None)
+    T.close()
+
+
+def test_mesh_or_layout_that_refuses_one_loop(times):
+    m = quad_mesh(23, 17, seed=8)
+    times[:] = [2.0, 3.0, 1.0, 4.0, 5.0]
+    T = make(m, layout="soa")
+    T.build_plans(flux_block_size=64)
+    T.autotune_flux(CANDIDATES)
+    assert T.whole_options is None and T.step_launches() > 2
+    T.close()
+    m.b2n[3] = m.b2n[3, ::-1]
+    T = make(m)
+    T.build_plans(flux_block_size=64)
+    T.autotune_flux(CANDIDATES)
+    assert T.whole_options is None and T.step_launches() > 2
+    T.close()
 
 
 def test_timed_loops_run_separately():
