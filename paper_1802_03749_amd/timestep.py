@@ -263,8 +263,25 @@ class TimeStep2D:
             if e.status not in (U.UM_ERR_UNSUPPORTED, U.UM_ERR_NOMEM):
                 raise
             return
+        if not self.fused and self.C > 800_000 and self._staged_cells(h) > 2 * self.C:
+            U.um_plan_destroy(h)
+            return
         self._whole = Plan(h, "hier", o.block_size, U.um_plan_stats_get(h).as_dict())
         self.whole_options = dict(flux_opts)
+
+    # A step whose adt is the old state's evaluates it for every cell that a
+    # block stages.  Chunks of the RCM order stage three cells per cell (bisected
+    # blocks of 512 edges 1.25), which the launches saved pay for on small meshes
+    # only.  Chunks of 256 edges, binary64 (binary32), one loop against separate
+    # ones: 720k cells 67.7 against 63.2 us (46.8, 48.6), 980k 87.2 against 78.9
+    # (60.2, 60.1), 2.88M 257 against 214 (177, 154); of 64 edges, 720k 73.3
+    # against 66.9 (54.1, 50.8), 2.88M 276 against 237.  Bisected blocks of 64
+    # (1.74 cells per cell) 59.0 against 60.0 at 720k.
+    @staticmethod
+    def _staged_cells(step_plan: int) -> int:
+        rec = np.empty(U.um_plan_export(step_plan, U.UM_EXP_OWNER_RECORDS), np.int32)
+        U.um_plan_export(step_plan, U.UM_EXP_OWNER_RECORDS, rec, rec.size)
+        return int(rec.reshape(-1, 10)[:, 2].sum(dtype=np.int64))
 
     def flux_args(self):
         a = U.um_arg

@@ -84,3 +84,36 @@ def test_timed_loops_run_separately():
     T.build_plans(flux_block_size=64)  # new plans are not timed
     assert T.step_launches() == whole
     T.close()
+
+
+@pytest.mark.parametrize("nx,fuse,order,whole", [
+    (890, False, "none", True), (900, False, "none", False), (900, True, "none", True),
+    (900, False, "partition", True)])
+def test_large_steps_of_redundant_blocks(nx, fuse, order, whole):
+    """Rows of edges stage three cells per owned cell: on more than 800,000
+    cells a step that evaluates adt for all of them runs as separate loops."""
+    m = rows(nx, 890)
+    T = TimeStep2D(m["x"], m["q"], m["e2n"], m["e2c"], m["b2n"], m["b2c"], m["c2n"], QINF,
+                   device=-1, block_size=256, order=order)
+    T.build_plans(flux_block_size=256, fuse_adt=fuse)
+    assert (T._whole is not None) == whole and (T.step_launches() == 2) == whole
+    T.close()
+
+
+def rows(nx, ny):
+    """An nx x ny quad grid, cells, nodes and edges numbered row by row."""
+    node = np.arange((nx + 1) * (ny + 1)).reshape(ny + 1, nx + 1)
+    cell = np.arange(nx * ny).reshape(ny, nx)
+    sw, se, ne, nw = node[:-1, :-1], node[:-1, 1:], node[1:, 1:], node[1:, :-1]
+    pairs = lambda a, b: np.stack([a.ravel(), b.ravel()], 1)
+    # the normal (y_b - y_a, x_a - x_b) of (a, b) points out of the first cell
+    edges = [(cell[:, :-1], cell[:, 1:], se[:, :-1], ne[:, :-1]),
+             (cell[:-1], cell[1:], ne[:-1], nw[:-1])]
+    l, r, a, b = (np.concatenate([e[k].ravel() for e in edges]) for k in range(4))
+    o = np.lexsort((r, l))
+    sides = [(cell[0], sw[0], se[0]), (cell[-1], ne[-1], nw[-1]),
+             (cell[:, 0], nw[:, 0], sw[:, 0]), (cell[:, -1], se[:, -1], ne[:, -1])]
+    bc, ba, bb = (np.concatenate([s[k].ravel() for s in sides]) for k in range(3))
+    x = np.stack([np.tile(np.arange(nx + 1.0), ny + 1), np.repeat(np.arange(ny + 1.0), nx + 1)], 1)
+    return dict(x=x, q=np.ones((nx * ny, 4)), e2n=pairs(a[o], b[o]), e2c=pairs(l[o], r[o]),
+                b2n=pairs(ba, bb), b2c=bc, c2n=np.stack([v.ravel() for v in (sw, se, ne, nw)], 1))
