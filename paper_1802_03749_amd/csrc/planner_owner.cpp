@@ -452,6 +452,32 @@ void build_owner_plan(const Ctx &ctx, const EdgeArgs &ea, const um_plan_opts &o,
     op.use = true;
 }
 
+// Elements of a dataflow hex loop above which its waiting kernel is the faster
+// one.  A brick of 8x8x4 elements evaluates 405 to 441 for its 256 nodes.  On
+// small meshes that costs less than waiting for eight block colours in turn; on
+// large ones the chain is hidden and the extra evaluations are not.  One sweep
+// in us, waiting -> owner kernel, MIN colouring, 256 elements per block unless
+// stated:
+//   AoS, barrier rounds: 24^3 elements 25.3 -> 6.0 (RECOLOUR), 104^3 52.2 -> 41.6,
+//     120^3 73.7 -> 61.5, 124^3 81.9 -> 77.3 (128 per block 101 -> 84), but 128^3
+//     73.4 -> 75.5.  Blocks of 512 were refused below 2,000,000 elements for what
+//     they stage; the bricks of 128^3 are not, and would gain.
+//   AoS, LDS atomics, whose single round makes a shorter chain: 104^3 48.8 -> 42.0,
+//     116^3 58.1 -> 56.3 (320 per block 61.2 -> 62.3), 120^3 64.6 -> 62.2 (320:
+//     64.9 -> 68.7), 124^3 68.5 -> 76.6 (128: 83.3 -> 84.1; but 64: 107 -> 91).
+//   SoA data wait longer: 124^3 88.8 -> 79.8, LDS atomics 80.5 -> 79.8.
+//   Blocks that are chunks of the RCM order evaluate up to 3.9 elements per
+//     element (64 per block; larger ones stage too much): AoS 80^3 61.9 -> 44.3,
+//     104^3 92.7 -> 92.3, 112^3 111 -> 115, 124^3 147 -> 167; LDS atomics 88^3
+//     58.8 -> 58.2, 96^3 69.8 -> 74.3; SoA 104^3 99.4 -> 97.1.
+// As launches the colours cost more at every size and in every order: 24^3 59.0
+// -> 5.9, 96^3 110 -> 33.4, 124^3 144 -> 77 (chunks, 64 per block: 194 -> 169),
+// 160^3 260 -> 175.
+static int64_t waiting_from(bool redundant, bool few_rounds, int32_t block_size) {
+    if (redundant) return few_rounds ? 800000 : 1200000;
+    return few_rounds && block_size >= 128 ? 1600000 : 2000000;
+}
+
 // The same for the hex loop: nodes are owned, a block evaluates every element
 // around its nodes.
 void build_owner_plan_hex(const Ctx &ctx, const HexArgs &ha, const um_plan_opts &o,
@@ -461,15 +487,10 @@ void build_owner_plan_hex(const Ctx &ctx, const HexArgs &ha, const um_plan_opts 
     const int32_t nb = int32_t(hp.blk_off.size()) - 1;
     OwnerPlan &op = hp.owner;
     op = OwnerPlan{};
-    // A brick of 8x8x4 elements evaluates 405 for its 256 nodes.  Up to about
-    // two million elements that costs less than waiting for eight block
-    // colours in turn; beyond, the chain is hidden and the extra evaluations
-    // are not.  One sweep, waiting -> owner kernel: 24^3 elements 22.5 -> 5.7
-    // us, 64^3 39.0 -> 11.9, 96^3 58.3 -> 34.5 (49.9 with MIN colouring), 120^3
-    // 80.9 -> 70.4, but 128^3 73.4 -> 75.5 and, with LDS atomics, 67.8 -> 75.6.
-    // As launches the colours cost more at every size: 24^3 54.4 -> 6.0, 96^3
-    // 117.1 -> 34.8, 128^3 121.0 -> 75.2, 160^3 260 -> 175.
-    if (nb <= 0 || (o.schedule == UM_SCHED_DATAFLOW && E > 2000000)) return;
+    if (nb <= 0) return;
+    const bool flow = o.schedule == UM_SCHED_DATAFLOW;
+    const bool few_rounds = ha.layout == UM_AOS && o.tcmode == UM_TC_LDS_ATOMIC;
+    if (flow && E > waiting_from(false, few_rounds, o.block_size)) return;
     Around ar;
     if (!ar.build(m, N, hp.blk_off, {8, MAX_NODE_ELEMENTS})) return;
     const auto &[D, own_off, own, inc, deg, owner] = ar;
@@ -552,7 +573,8 @@ void build_owner_plan_hex(const Ctx &ctx, const HexArgs &ha, const um_plan_opts 
         lanes = std::max({lanes, r.nn, r.n_own});
     }
     op.threads = (lanes + 63) / 64 * 64;
-    if (res != 0 || op.threads > 1024 || rows > int64_t(INT32_MAX) ||
+    const bool slow = flow && E > waiting_from(2 * rows > 5 * E, few_rounds, o.block_size);
+    if (res != 0 || slow || op.threads > 1024 || rows > int64_t(INT32_MAX) ||
         op.lds > (o.lds_limit_bytes > 0 ? o.lds_limit_bytes : ctx.lds_limit)) {
         op = OwnerPlan{};
         return;
