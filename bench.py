@@ -13,10 +13,11 @@ colour as in the paper).  Inputs are seeded synthetic data
 resident in HBM before timing starts; the plan is built once beforehand and
 its build time is reported separately.
 
-Prints one JSON line to stdout; progress goes to stderr.  Besides the
-headline it reports: the global-colouring and atomics baselines on the same
-GPU and mesh (each at its best of RCM / RCM + partition order and AoS /
-SoA layout), the FP32-storage
+Prints one JSON line to stdout, short enough for a harness that keeps the end
+of the output; --full FILE writes the record of every measurement, and
+progress goes to stderr.  Besides the headline it measures the
+global-colouring and atomics baselines on the same GPU and mesh (each at its
+best of RCM / RCM + partition order and AoS / SoA layout), the FP32-storage
 variant, the 3D hexahedral element loop (128^3 elements) with its own
 baselines, a batch of 64 meshes of uneven size (5k-500k cells) advanced by
 full time steps as one union and one mesh at a time (eager and replayed
@@ -116,6 +117,38 @@ def cold_sweep_seconds(torch, run, steps: int) -> float:
     return sum(ms) / len(ms) * 1e-3
 
 
+def runs_owner_kernel(loop, plan, U) -> bool:
+    """Whether the plan's blocks run without an order (the owner kernel), so
+    that schedule, colours, rounds and sum-first blocks only describe it."""
+    try:
+        return loop.export(plan, U.UM_EXP_OWNER_RECORDS).size > 0
+    except U.UmeshError:
+        return False
+
+
+def brief(out: dict) -> dict:
+    """The record's headline, and of the other measurements their times only."""
+    def times(d, keys):
+        return {k: {q: round(v[q], 5) for q in keys if q in v} for k, v in d.items()
+                if isinstance(v, dict)}
+    ms = ("ms_per_step", "ms_per_step_eager", "ms_per_step_graph")
+    b = {k: out[k] for k in ("metric", "value", "unit", "n_gpus", "steps", "warmup", "ms_per_step",
+                             "higher_is_better", "scaling", "vs_baseline", "dtype", "data",
+                             "config", "useful_gbps", "useful_bytes_per_step",
+                             "pct_hbm_peak_step", "roofline", "roofline_cold",
+                             "device_copy_gbps")}
+    cpu = out["cpu_baseline"]
+    if cpu:
+        b["cpu_baseline"] = {k: cpu[k] for k in ("value", "unit", "cores", "kind")}
+        b["cpu_baseline"]["all_cores"] = {k: cpu["all_cores"][k] for k in ("value", "cores")}
+    b["baselines"] = {k: {q: v[q] for q in ("order", "layout", "ms_per_step", "hier_speedup")}
+                      for k, v in out["baselines"].items()}
+    b["variants"] = times(out["variants"], ms)
+    b["extras"] = {k: ({q: v[q] for q in ms if q in v} or times(v, ms))
+                   for k, v in out["extras"].items()}
+    return b
+
+
 def cpu_model() -> str:
     try:
         with open("/proc/cpuinfo") as f:
@@ -149,10 +182,14 @@ def run_sweep(torch, args, U):
         s = time_steps(torch, lambda: L.run(p), steps, warm)
         if U.um_plan_errors(p.handle) != 0:
             raise RuntimeError("a dataflow wait timed out in the sweep")
-        return {"us_per_sweep": s * 1e6, "edges_per_s": E / s, "useful_gbps": useful / s / 1e9,
-                "launches": p.stats["n_launches"], "block_colours": p.stats["n_block_colours"],
-                "global_colours": p.stats["n_global_colours"],
-                "sum_first_blocks": p.stats["n_sum_first_blocks"]}
+        r = {"us_per_sweep": s * 1e6, "edges_per_s": E / s, "useful_gbps": useful / s / 1e9,
+             "launches": p.stats["n_launches"], "block_colours": p.stats["n_block_colours"],
+             "global_colours": p.stats["n_global_colours"]}
+        if runs_owner_kernel(L, p, U):
+            r["kernel"] = "owner_kernel"
+        else:
+            r["sum_first_blocks"] = p.stats["n_sum_first_blocks"]
+        return r
 
     def hier_entries(L, order, S, plans):
         for name, kw in plans:
@@ -181,7 +218,8 @@ def run_sweep(torch, args, U):
             ent[f"rcm+partition/{strat}/S{S}"] = timed(L, L.plan(strat, S))
         extra = ()
         if args.gather == "lds_dma":
-            # every block loading its residuals early instead (none sums first)
+            # every block loading its residuals early instead (none sums first);
+            # the same measurement again where the owner kernel runs
             extra = (("dataflow_no_sum_first", dict(df[1], sum_first="never")),)
         hier_entries(L, "rcm+partition", S, (cl, df) + extra)
         L.close()
@@ -208,7 +246,10 @@ def tile_blocks(mesh, tx: int, ty: int) -> np.ndarray:
 
 
 def run_ablations(torch, mesh, S, args, useful, E):
-    """One knob at a time around the headline configuration."""
+    """One knob at a time around the headline configuration.  An entry whose
+    kernel is the owner kernel differs from another one in its blocks and its
+    launch order only: no other knob reaches that kernel."""
+    from paper_1802_03749_amd import umesh as U
     from paper_1802_03749_amd.edgeloop import EdgeFluxLoop
     steps, warm = max(args.steps // 4, 10), max(args.warmup // 4, 2)
     out = {}
@@ -219,7 +260,8 @@ def run_ablations(torch, mesh, S, args, useful, E):
         return {"us_per_sweep": s * 1e6, "useful_gbps": useful / s / 1e9,
                 "pct_hbm_peak": 100 * useful / s / 1e9 / 8000.0, "launches": st["n_launches"],
                 "block_colours": st["n_block_colours"], "global_colours": st["n_global_colours"],
-                "reuse_factor": st["reuse_factor"]}
+                "reuse_factor": st["reuse_factor"],
+                **({"kernel": "owner_kernel"} if runs_owner_kernel(L, p, U) else {})}
 
     base = dict(staging=args.staging, tcmode=args.tcmode, block_colouring=args.bcol,
                 schedule=args.schedule, elems_per_thread=args.ept)
@@ -310,6 +352,8 @@ def main() -> int:
     ap.add_argument("--no-ablations", action="store_true",
                     help="skip the ablation matrix (partitioner, order, layout, staging, colour "
                          "rounds, block colouring, schedule, gather, wave-pure colour groups)")
+    ap.add_argument("--full", default="",
+                    help="write the record of every measurement to this file (JSON)")
     ap.add_argument("--no-sweep", action="store_true",
                     help="skip the 1200x600 order x strategy x block-size sweep")
     args = ap.parse_args()
@@ -351,10 +395,7 @@ def main() -> int:
         hopts["gather"] = args.gather
     plan = hier.plan("hier", S, schedule=args.schedule, **hopts)
     st = plan.stats
-    try:
-        owned = hier.export(plan, U.UM_EXP_OWNER_RECORDS).size > 0
-    except U.UmeshError:
-        owned = False
+    owned = runs_owner_kernel(hier, plan, U)
     log(f"reorder {reorder_s:.1f}s, plan {st['build_seconds']:.2f}s: blocks={st['n_blocks']} "
         f"block colours={st['n_block_colours']} thread colours<={st['max_thread_colours']} "
         f"reuse={st['reuse_factor']:.3f} lds={st['lds_bytes_max']} launches={st['n_launches']}")
@@ -702,11 +743,15 @@ def main() -> int:
         "sweep_1200x600": sweep,
         "plan": {k: st[k] for k in ("n_blocks", "n_block_colours", "max_thread_colours",
                                      "avg_thread_colours", "reuse_factor", "lds_bytes_max",
-                                     "staged_points", "plan_device_bytes", "build_seconds")},
+                                     "staged_points", "plan_device_bytes", "build_seconds")
+                 if not (owned and k == "lds_bytes_max")},
         "reorder_seconds": reorder_s,
         "device_copy_gbps": copy_gbps,
     }
-    print(json.dumps(out), flush=True)
+    if args.full:
+        with open(args.full, "w") as f:
+            json.dump(out, f)
+    print(json.dumps(brief(out)), flush=True)
     return 0
 
 
