@@ -135,9 +135,10 @@ typedef enum { UM_BCOL_FIRST_FIT = 0, UM_BCOL_RECOLOUR = 1, UM_BCOL_MIN = 2 } um
  *   (binary32: and two elements per lane).
  *   Hex loop: no node has more than 16 elements, no block stages more than
  *   1022 nodes or evaluates more than 1024 elements, 24 * (nodes) is below
- *   2^31; DATAFLOW plans have at most 2,000,000 elements (AoS data with LDS
- *   atomics 1,600,000; blocks that together evaluate more than 2.5 times the
- *   elements 1,200,000, or 800,000), above which their order is faster.
+ *   2^31; DATAFLOW plans have at most 2,000,000 elements (in blocks of 128 and
+ *   more, AoS data with LDS atomics 1,600,000; where the blocks together
+ *   evaluate more than 2.5 times the elements 1,200,000, or AoS data with LDS
+ *   atomics 800,000): above, keeping their order is faster.
  *   Both: a block's staged data (hex: and sums) fit the LDS limit.
  * All other plans keep the order of their schedule.  UM_EXP_OWNER_RECORDS is
  * defined for owner plans only, and tells them apart.  An owner plan's block

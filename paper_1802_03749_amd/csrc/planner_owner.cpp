@@ -471,8 +471,8 @@ void build_owner_plan(const Ctx &ctx, const EdgeArgs &ea, const um_plan_opts &o,
 //     104^3 92.7 -> 92.3, 112^3 111 -> 115, 124^3 147 -> 167; LDS atomics 88^3
 //     58.8 -> 58.2, 96^3 69.8 -> 74.3; SoA 104^3 99.4 -> 97.1.
 // As launches the colours cost more at every size and in every order: 24^3 59.0
-// -> 5.9, 96^3 110 -> 33.4, 124^3 144 -> 77 (chunks, 64 per block: 194 -> 169),
-// 160^3 260 -> 175.
+// -> 5.9, 96^3 110 -> 33.4, 124^3 144 -> 77, 160^3 258 -> 189 (chunks, 64 per
+// block: 124^3 194 -> 169, 160^3 382 -> 362).
 static int64_t waiting_from(bool redundant, bool few_rounds, int32_t block_size) {
     if (redundant) return few_rounds ? 800000 : 1200000;
     return few_rounds && block_size >= 128 ? 1600000 : 2000000;
