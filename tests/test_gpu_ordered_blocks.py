@@ -52,19 +52,18 @@ def ordered(L, p):
     return e.value.status == U.UM_ERR_STATE
 
 
-@pytest.mark.parametrize("schedule,gather,sum_first", [
-    ("colour_launches", "registers", "auto"), ("dataflow", "registers", "always"),
-    ("dataflow", "registers", "never"), ("dataflow", "lds_dma", "always"),
-    ("dataflow", "lds_dma", "never")])
+@pytest.mark.parametrize("schedule,gather,sum_first,layout", [
+    (*form, layout) for layout in ("aos", "soa") for form in (
+        ("colour_launches", "registers", "auto"), ("dataflow", "registers", "always"),
+        ("dataflow", "registers", "never"), ("dataflow", "lds_dma", "always"),
+        ("dataflow", "lds_dma", "never"))
+    if layout == "aos" or form[1] != "lds_dma"])  # the LDS-DMA gather reads AoS records
 @pytest.mark.parametrize("dtype", ["f64", "f32"])
-@pytest.mark.parametrize("layout", ["aos", "soa"])
 @pytest.mark.parametrize("nx,ny,S", [(47, 33, 128), (9, 7, 512), (150, 90, 512)])
 def test_edge_kernels(nx, ny, S, layout, dtype, schedule, gather, sum_first):
     """Every form of the ordered edge kernels: edges per lane, rounds of thread
     colours or LDS atomics, colour groups of whole wavefronts, XCD groups, id
     lists; rounds repeat bit for bit, and XCD groups leave them as they are."""
-    if gather == "lds_dma" and layout == "soa":
-        pytest.skip("the LDS-DMA gather reads AoS records")
     m = quads_with_hub(nx, ny)
     L = EdgeFluxLoop(m.x, m.q, m.adt, m.e2n, m.e2c, device=0, layout=layout, dtype=dtype,
                      block_size=S, point_reorder=2)
